@@ -283,6 +283,14 @@ swiftcl_status swiftcl_cl_backward_timed(swiftcl_plan_t plan, const swiftcl_inpu
 swiftcl_status swiftcl_cl_kgrowth(swiftcl_plan_t plan, const swiftcl_inputs* in, const double* D_kz, void* C,
                                   void* stream);
 
+/* swiftcl_cl_kgrowth by the sums of its adjoint: the windows from the FFTLog coefficients of every
+ * node, continued along ln k, as swiftcl_cl_kgrowth_backward recomputes them.  The two entry points
+ * agree to FP32 rounding; the gradient with respect to the biases is formed from C, so a program that
+ * needs it bit for bit with the adjoint's windows calls this one (about four times slower).  Same
+ * arguments and refusals. */
+swiftcl_status swiftcl_cl_kgrowth_nodes(swiftcl_plan_t plan, const swiftcl_inputs* in, const double* D_kz, void* C,
+                                        void* stream);
+
 /* Reverse-mode derivative of L = sum dC C for the scale-dependent growth path (the paper
  * differentiates its pipeline end to end, Sec. 1): the windows of swiftcl_cl_kgrowth are
  * recomputed (as W, FP32), Y = G W on MFMA gives dL/dP(k_j) = (2/pi) w_j k_j^3 sum_l sum_t W Y, and

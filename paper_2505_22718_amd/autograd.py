@@ -82,7 +82,8 @@ class ClKgrowthFunction(torch.autograd.Function):
         t = dict(inputs)
         t.update(pk=pk.detach().contiguous(), bias=bias.detach().contiguous())
         D = D_kz.detach().contiguous()
-        C = plan.cl_kgrowth(t, D)
+        # dL/db is formed from C, so C then comes from the windows that the adjoint sums
+        C = plan.cl_kgrowth_nodes(t, D) if ctx.needs_input_grad[4] else plan.cl_kgrowth(t, D)
         ctx.plan = plan
         ctx.t = t
         ctx.D = D

@@ -84,7 +84,7 @@ EXPORTED = ["swiftcl_plan", "swiftcl_plan_destroy", "swiftcl_last_error", "swift
             "swiftcl_windows", "swiftcl_cl", "swiftcl_cl_timed", "swiftcl_cl_backward",
             "swiftcl_cl_backward_timed", "swiftcl_autotune", "swiftcl_set_launch", "swiftcl_get_launch",
             "swiftcl_cl_kgrowth", "swiftcl_cl_limber", "swiftcl_cl_noalloc", "swiftcl_plan_info",
-            "swiftcl_cl_limber_backward", "swiftcl_cl_kgrowth_backward"]
+            "swiftcl_cl_limber_backward", "swiftcl_cl_kgrowth_backward", "swiftcl_cl_kgrowth_nodes"]
 
 _lib = None
 
@@ -108,6 +108,7 @@ def load(path: str = LIB_PATH):
     lib.swiftcl_cl_noalloc.argtypes = [vp, ctypes.POINTER(swiftcl_inputs), vp, vp]
     lib.swiftcl_cl_timed.argtypes = [vp, ctypes.POINTER(swiftcl_inputs), vp, vp, ctypes.POINTER(ctypes.c_float)]
     lib.swiftcl_cl_kgrowth.argtypes = [vp, ctypes.POINTER(swiftcl_inputs), vp, vp, vp]
+    lib.swiftcl_cl_kgrowth_nodes.argtypes = [vp, ctypes.POINTER(swiftcl_inputs), vp, vp, vp]
     lib.swiftcl_cl_limber.argtypes = [vp, ctypes.POINTER(swiftcl_inputs), vp, vp]
     lib.swiftcl_cl_backward.argtypes = [vp, ctypes.POINTER(swiftcl_inputs), vp, vp, vp, vp, vp, ctypes.c_uint32, vp]
     lib.swiftcl_cl_limber_backward.argtypes = [vp, ctypes.POINTER(swiftcl_inputs), vp, vp, vp, vp, vp, vp]
@@ -174,6 +175,11 @@ def swiftcl_cl_noalloc(plan, inputs: swiftcl_inputs, C: int, stream: int = 0):
 
 def swiftcl_cl_kgrowth(plan, inputs: swiftcl_inputs, D_kz: int, C: int, stream: int = 0):
     _check(load().swiftcl_cl_kgrowth(plan, ctypes.byref(inputs), ctypes.c_void_p(D_kz), ctypes.c_void_p(C),
+                                     ctypes.c_void_p(stream)))
+
+
+def swiftcl_cl_kgrowth_nodes(plan, inputs: swiftcl_inputs, D_kz: int, C: int, stream: int = 0):
+    _check(load().swiftcl_cl_kgrowth_nodes(plan, ctypes.byref(inputs), ctypes.c_void_p(D_kz), ctypes.c_void_p(C),
                                      ctypes.c_void_p(stream)))
 
 

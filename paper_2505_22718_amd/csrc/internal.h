@@ -120,6 +120,20 @@ struct plan_dev {
   void* kg_m;         // same layout: their second derivatives along ln k
   int* kg_perm;       // [vchunk][max_ell] multipole slots grouped by band
   int* kg_tile;       // [vchunk][kg_ntile][4] band, first entry of kg_perm, count, 0
+  // the same by the product over the chi nodes of the support (kgrowth_conv.hip)
+  int kc_chunk;       // points per chunk (of vbuf too)
+  int kc_ns;          // chi nodes a support may hold: N - m0
+  int kc_sp;          // entries per growth row (kc_dt); kc_f rows hold 16 more
+  int kc_sk;          // entries per K_l row
+  double* kc_w;       // [n_k][4] spline weights of D_a, D_{a+1}, M_a, M_{a+1} at k_j
+  double* kc_ip;      // [n_interp] 1 / pivot of the node spline's tridiagonal system
+  double2* kc_u;      // [kind][n_ell][M] the U table in FP64
+  double2* kc_tw;     // [N] the twiddles in FP64
+  double* kc_dn;      // [kc_chunk][n_interp][kc_ns] growth of the nodes on the chi nodes m0 ..
+  double* kc_dm;      // same layout: its second derivatives along ln k
+  float* kc_dt;       // [vchunk][n_k up to 16][kc_sp] D_j on the chi nodes, shifted by j % 16
+  float* kc_f;        // [kc_chunk][T][kc_sp + 16] band-0 kernel samples, padded with zeros
+  float* kc_k;        // [kc_chunk][kind][max_ell][kc_sk] the rows K_l(s), s = m0 ..
 };
 
 // Tracer kind of slot t of point b as the kernels use it: a value outside the three kinds reads as
@@ -164,6 +178,10 @@ hipError_t launch_windows_w(const plan_dev& p, const swiftcl_inputs* in, int b0,
 // C of points [b0, b0 + nbp) from the V rows in the workspace (vbuf)
 hipError_t launch_contract(const plan_dev& p, const swiftcl_inputs* in, void* C, int b0, int nbp, hipStream_t s);
 hipError_t launch_kgrowth(const plan_dev& p, const swiftcl_inputs* in, const double* D_kz, void* C, hipStream_t s);
+// the same C by the product over the support (kgrowth_conv.hip)
+hipError_t launch_kgrowth_conv(const plan_dev& p, const swiftcl_inputs* in, const double* D_kz, void* C, hipStream_t s);
+void kgrowth_conv_sizes(plan_dev& p);          // sets kc_ns, kc_sp and kc_sk
+size_t kgrowth_conv_bytes(const plan_dev& p);  // then its workspace per point, but for vbuf
 hipError_t launch_kgrowth_backward(const plan_dev& p, const swiftcl_inputs* in, const double* D_kz, const void* C,
                                    const void* dC, double* dpk, double* dbias, hipStream_t s);
 hipError_t launch_bwd_gv(const plan_dev& p, const swiftcl_inputs* in, const void* dC, int b0, int nbp, hipStream_t s);

@@ -185,6 +185,9 @@ hipError_t launch_u_table(const plan_dev& pd, const double* d_ell, hipStream_t s
   else
     hipLaunchKernelGGL(k_u_table<float>, grid, dim3(128), 0, s, (float2*)p->U, d_ell, p->ell_band, p->fell, bt,
                        p->n_ell, p->M, p->delta, p->taper_frac);
+  if (p->n_interp > 0)
+    hipLaunchKernelGGL(k_u_table<double>, grid, dim3(128), 0, s, p->kc_u, d_ell, p->ell_band, p->fell, bt, p->n_ell,
+                       p->M, p->delta, p->taper_frac);
   if (p->rsd)  // RSD and magnification plans are FP32 / split
     hipLaunchKernelGGL(k_u_rsd<float>, grid, dim3(128), 0, s, (float2*)p->UR, d_ell, p->ell_band, bt, p->n_ell, p->M,
                        p->delta, p->taper_frac);
@@ -328,7 +331,8 @@ static void free_plan(swiftcl_plan_s* p) {
                   p->d.lu_nz, p->d.z_union, p->d.union_iv, p->d.pt, p->d.m_chi, p->d.m_D, p->d.m_ia, p->d.m_n, p->d.lens_q, p->d.phase, p->d.node_f, p->d.node_i, p->d.ddD_part, p->d.g,
                   p->d.chat, p->d.sqrt_s, p->d.kss, p->d.flags, p->d.dchat_part, p->d.dpk_part, p->d.dg, p->d.sched, p->d.bwd_order, p->d.vbuf,
                   p->d.kg_ones, p->d.kg_ia, p->d.kg_w, p->d.kg_ip, p->d.kg_uh, p->d.kg_c, p->d.kg_m, p->d.kg_perm,
-                  p->d.kg_tile, p->d.UR, p->d.g_r, p->d.chat_r, p->d.Umu, p->d.g_mu, p->d.chat_mu};
+                  p->d.kg_tile, p->d.kc_w, p->d.kc_ip, p->d.kc_u, p->d.kc_tw, p->d.kc_dn, p->d.kc_dm, p->d.kc_dt,
+                  p->d.kc_f, p->d.kc_k, p->d.UR, p->d.g_r, p->d.chat_r, p->d.Umu, p->d.g_mu, p->d.chat_mu};
   for (void* q : ptrs)
     if (q) (void)hipFree(q);
   delete p;
@@ -579,11 +583,17 @@ extern "C" swiftcl_status swiftcl_plan(const swiftcl_plan_desc* d, void* stream,
     if (chunk < 1) chunk = 1;
     if (chunk > (size_t)B) chunk = B;
     p->d.vchunk = (int)chunk;
+    if (p->d.n_interp > 0) {
+      kgrowth_conv_sizes(p->d);
+      const size_t fit = std::max((size_t)1, ((size_t)4 << 30) / (per_point + kgrowth_conv_bytes(p->d)));
+      p->d.kc_chunk = (int)std::min(fit, (size_t)B);
+      chunk = std::max(chunk, (size_t)p->d.kc_chunk);
+    }
     ALLOC(vbuf, char, chunk * per_point);
   }
   std::vector<int> kg_ia;
   std::vector<float> kg_w, kg_ip;
-  std::vector<double> kg_ones;
+  std::vector<double> kg_ones, kc_w, kc_ip;
   if (p->d.n_interp > 0) {
     const int A = p->d.n_interp;
     const size_t chunk = p->d.vchunk;
@@ -597,31 +607,41 @@ extern "C" swiftcl_status swiftcl_plan(const swiftcl_plan_desc* d, void* stream,
     ALLOC(kg_m, char, chunk * T * nb * A * M * 8);
     ALLOC(kg_perm, int, chunk * p->d.max_ell);
     ALLOC(kg_tile, int, chunk * p->d.kg_ntile * 4);
+    const size_t kcc = p->d.kc_chunk;
+    ALLOC(kc_w, double, (size_t)4 * nk);
+    ALLOC(kc_ip, double, A);
+    ALLOC(kc_u, double2, (size_t)SWIFTCL_NKINDS * p->d.n_ell * M);
+    ALLOC(kc_tw, double2, N);
+    ALLOC(kc_dn, double, kcc * A * p->d.kc_ns);
+    ALLOC(kc_dm, double, kcc * A * p->d.kc_ns);
+    ALLOC(kc_dt, float, kcc * ((nk + 15) / 16 * 16) * p->d.kc_sp);
+    ALLOC(kc_f, float, kcc * T * (p->d.kc_sp + 16));
+    ALLOC(kc_k, float, kcc * SWIFTCL_NKINDS * p->d.max_ell * p->d.kc_sk);
     // natural spline through the nodes, uniform in ln k: interval, offset and weights of every k node
     const double lk0 = std::log(d->k[0]);
     const double h = (std::log(d->k[nk - 1]) - lk0) / (A - 1);
     kg_ia.resize(nk);
-    kg_w.resize((size_t)4 * nk);
+    kc_w.resize((size_t)4 * nk);
     for (int j = 0; j < nk; ++j) {
       const double u = (std::log(d->k[j]) - lk0) / h;
       const int a = std::min(std::max((int)std::floor(u), 0), A - 2);
       const double tt = u - a, ut = 1.0 - tt;
       kg_ia[j] = a;
-      kg_w[4 * (size_t)j] = (float)ut;
-      kg_w[4 * (size_t)j + 1] = (float)tt;
-      kg_w[4 * (size_t)j + 2] = (float)(h * h / 6.0 * (ut * ut * ut - ut));
-      kg_w[4 * (size_t)j + 3] = (float)(h * h / 6.0 * (tt * tt * tt - tt));
+      const double w[4] = {ut, tt, h * h / 6.0 * (ut * ut * ut - ut), h * h / 6.0 * (tt * tt * tt - tt)};
+      for (int q = 0; q < 4; ++q) kc_w[4 * (size_t)j + q] = w[q];
     }
+    kg_w.assign(kc_w.begin(), kc_w.end());
     // node rows a 64-node k tile of the windows GEMM reads (its intervals and the one after the last)
     int rows = 0;
     for (int j0 = 0; j0 < nk; j0 += 64) rows = std::max(rows, kg_ia[std::min(j0 + 63, nk - 1)] - kg_ia[j0] + 2);
     p->d.kg_stage = rows <= 16 ? 1 : 0;
-    kg_ip.assign(A, 0.f);
+    kc_ip.assign(A, 0.0);
     double ip = 0.0;
     for (int a = 1; a + 1 < A; ++a) {
       ip = 1.0 / (4.0 - ip);
-      kg_ip[a] = (float)ip;
+      kc_ip[a] = ip;
     }
+    kg_ip.assign(kc_ip.begin(), kc_ip.end());
     kg_ones.assign((size_t)B * p->d.n_zg, 1.0);
   }
   p->d.sched_stride = sched_stride_for(B);
@@ -679,7 +699,10 @@ extern "C" swiftcl_status swiftcl_plan(const swiftcl_plan_desc* d, void* stream,
     const Up kg[] = {{p->d.kg_ones, kg_ones.data(), kg_ones.size() * sizeof(double)},
                      {p->d.kg_ia, kg_ia.data(), kg_ia.size() * sizeof(int)},
                      {p->d.kg_w, kg_w.data(), kg_w.size() * sizeof(float)},
-                     {p->d.kg_ip, kg_ip.data(), kg_ip.size() * sizeof(float)}};
+                     {p->d.kg_ip, kg_ip.data(), kg_ip.size() * sizeof(float)},
+                     {p->d.kc_w, kc_w.data(), kc_w.size() * sizeof(double)},
+                     {p->d.kc_ip, kc_ip.data(), kc_ip.size() * sizeof(double)},
+                     {p->d.kc_tw, twd.data(), twd.size() * sizeof(double)}};
     for (auto& u : kg) {
       e = hipMemcpyAsync(u.dst, u.src, u.n, hipMemcpyHostToDevice, s);
       if (e != hipSuccess) break;
@@ -809,8 +832,9 @@ extern "C" swiftcl_status swiftcl_cl_timed(swiftcl_plan_t p, const swiftcl_input
   return hip_check(e, "timed forward");
 }
 
-extern "C" swiftcl_status swiftcl_cl_kgrowth(swiftcl_plan_t p, const swiftcl_inputs* in, const double* D_kz, void* C,
-                                             void* stream) {
+// nodes: through the node coefficients (kgrowth.hip), else the product over the support
+static swiftcl_status run_kgrowth(swiftcl_plan_t p, const swiftcl_inputs* in, const double* D_kz, void* C, void* stream,
+                                  bool nodes) {
   if (!p) { set_error("plan is NULL"); return SWIFTCL_E_INVALID; }
   if (!in) { set_error("inputs is NULL"); return SWIFTCL_E_INVALID; }
   if (!D_kz || !C) { set_error("D_kz or C is NULL"); return SWIFTCL_E_INVALID; }
@@ -837,8 +861,19 @@ extern "C" swiftcl_status swiftcl_cl_kgrowth(swiftcl_plan_t p, const swiftcl_inp
   p->fwd_valid = false;
   hipError_t e = launch_assemble(p->d, &in1, s);
   if (e == hipSuccess) e = launch_sqrt_s(p->d, &in1, s);
-  if (e == hipSuccess) e = launch_kgrowth(p->d, &in1, D_kz, C, s);
+  if (e == hipSuccess)
+    e = nodes ? launch_kgrowth(p->d, &in1, D_kz, C, s) : launch_kgrowth_conv(p->d, &in1, D_kz, C, s);
   return hip_check(e, "scale-dependent growth launch");
+}
+
+extern "C" swiftcl_status swiftcl_cl_kgrowth(swiftcl_plan_t p, const swiftcl_inputs* in, const double* D_kz, void* C,
+                                             void* stream) {
+  return run_kgrowth(p, in, D_kz, C, stream, false);
+}
+
+extern "C" swiftcl_status swiftcl_cl_kgrowth_nodes(swiftcl_plan_t p, const swiftcl_inputs* in, const double* D_kz,
+                                                   void* C, void* stream) {
+  return run_kgrowth(p, in, D_kz, C, stream, true);
 }
 
 extern "C" swiftcl_status swiftcl_cl_kgrowth_backward(swiftcl_plan_t p, const swiftcl_inputs* in, const double* D_kz,

@@ -241,11 +241,18 @@ class Plan:
 
     def cl_kgrowth(self, t, D_kz, out=None):
         """C_l with scale-dependent growth: D_kz [B][n_interp][n_zg] float64 on the plan's device."""
+        return self._cl_kgrowth(bd.swiftcl_cl_kgrowth, t, D_kz, out)
+
+    def cl_kgrowth_nodes(self, t, D_kz, out=None):
+        """cl_kgrowth by the sums of its adjoint (swiftcl_cl_kgrowth_nodes); equal to rounding."""
+        return self._cl_kgrowth(bd.swiftcl_cl_kgrowth_nodes, t, D_kz, out)
+
+    def _cl_kgrowth(self, call, t, D_kz, out):
         s = self.inputs_struct(t)
         check_tensor("D_kz", D_kz, (s.batch, self.n_interp, len(self.z_geom)), torch.float64, self.device)
         out = self._cl_buffer("out", out, s.batch)
         self._new_state()
-        bd.swiftcl_cl_kgrowth(self.handle, s, D_kz.data_ptr(), out.data_ptr(), self._stream())
+        call(self.handle, s, D_kz.data_ptr(), out.data_ptr(), self._stream())
         return out
 
     def kgrowth_backward(self, t, D_kz, C, dC, want=("pk", "bias")):

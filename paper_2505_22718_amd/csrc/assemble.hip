@@ -13,22 +13,25 @@
 // outside [m0, m1]: the DFT of g is then the trapezoid rule of the cut kernel.
 //
 // One workgroup of GEOM_THREADS threads owns one parameter point and keeps all of its samples in LDS:
-// every spline is solved by one wavefront (the Thomas recurrences as parallel affine-map scans),
-// and the threads assemble g of the clustering tracers node by node; the lensing tracers follow
-// in k_geom_lens (one workgroup each: interval integrals, suffix scans, q at every node).
+// the chi and D splines are solved by the whole workgroup, the n(z) splines by one wavefront each (the
+// Thomas recurrences as parallel affine-map scans), and the threads assemble g of the clustering tracers
+// node by node; the lensing tracers follow in k_geom_lens (one workgroup each: interval integrals, suffix
+// scans, q at every node).
 #include "common.h"
 #include "geometry.h"
 #include "internal.h"
 
 // tracers whose n(z) rows sit in LDS at once
 #define GEOM_GROUP 16
-// threads per point: two chi nodes of state per thread (n_chi <= 2048) fit 128 VGPRs without
-// spilling, and the n(z) splines of up to 16 tracers run in one round of wavefronts
+// threads per point: the n(z) splines of up to 16 tracers run in one round of wavefronts
 #define GEOM_THREADS 1024
+#define GEOM_SCAN block_scan_doubles(2, GEOM_THREADS)
 
 size_t geometry_lds_bytes(const plan_dev& p) {
   const size_t tg = p.max_tracers < GEOM_GROUP ? p.max_tracers : GEOM_GROUP;
-  return sizeof(double) * ((size_t)7 * p.n_zg + (size_t)3 * p.n_zs + (size_t)2 * tg * p.n_zs);
+  // (the spline scans run in the space of the 1/h row, or after everything where that is too short)
+  const size_t scan = p.n_zg < GEOM_SCAN ? GEOM_SCAN : 0;
+  return sizeof(double) * ((size_t)7 * p.n_zg + (size_t)3 * p.n_zs + (size_t)2 * tg * p.n_zs + scan);
 }
 
 template <typename R>
@@ -61,9 +64,9 @@ __global__ __launch_bounds__(GEOM_THREADS) void k_geometry(plan_dev P, swiftcl_i
 
   const double* chig = in.chi_z + (size_t)b * nzg;
   const double* Dg = in.D_z + (size_t)b * nzg;
+  double* scan = nzg < GEOM_SCAN ? mia + nzg : zgih;
   for (int i = tid; i < nzg; i += nth) {
     zg[i] = P.z_geom[i];
-    zgih[i] = P.lu_geom[3 * nzg + i];
     chi[i] = chig[i];
     Dz[i] = Dg[i];
   }
@@ -71,25 +74,30 @@ __global__ __launch_bounds__(GEOM_THREADS) void k_geometry(plan_dev P, swiftcl_i
     zs[i] = P.z_nz[i];
     zsih[i] = P.lu_nz[3 * nzs + i];
   }
-  __syncthreads();
-
-  // splines of chi(z), D(z) and A_IA(z), one wavefront each
+  // splines of chi(z), D(z) and A_IA(z)
   const double* iag = in.ia ? in.ia + (size_t)b * nzg : nullptr;
-  if (wave == 0) wave_spline(chi, P.lu_geom, nzg, mchi, lane);
-  else if (wave == 1) wave_spline(Dz, P.lu_geom, nzg, mD, lane);
-  else if (wave == 2 && iag) {
-    bool bad = false;
-    for (int i = lane; i < nzg; i += SWIFTCL_WAVE) bad |= !isfinite(iag[i]);
-    if (bad) atomicOr(P.flags, FLAG_NONFINITE);
-    wave_spline(iag, P.lu_geom, nzg, mia, lane);
-  }
   __syncthreads();
+  {
+    const double* const y[2] = {chi, Dz};
+    double* const mo[2] = {mchi, mD};
+    block_spline<2>(y, P.lu_geom, nzg, mo, scan);
+  }
+  if (iag) {
+    bool bad = false;
+    for (int i = tid; i < nzg; i += nth) bad |= !isfinite(iag[i]);
+    if (bad) atomicOr(P.flags, FLAG_NONFINITE);
+    const double* const y[1] = {iag};
+    double* const mo[1] = {mia};
+    block_spline<1>(y, P.lu_geom, nzg, mo, scan);
+  }
   // keep the spline coefficients for the lensing kernels and the adjoint
   for (int i = tid; i < nzg; i += nth) {
     P.m_chi[(size_t)b * nzg + i] = mchi[i];
     P.m_D[(size_t)b * nzg + i] = mD[i];
     if (iag) P.m_ia[(size_t)b * nzg + i] = mia[i];
+    zgih[i] = P.lu_geom[3 * nzg + i];
   }
+  __syncthreads();
 
   // per-point scalars
   const double chi_min = chi[0], chi_max = chi[nzg - 1];
@@ -125,42 +133,36 @@ __global__ __launch_bounds__(GEOM_THREADS) void k_geometry(plan_dev P, swiftcl_i
     pt[PT_LNK0CHI0] = log(P.k0) + lchi0;
     pt[PT_M1] = m1d;
     pt[PT_THETA] = theta;
-    for (int kind = 0; kind < SWIFTCL_NKINDS; ++kind)
-      for (int bi = 0; bi < SWIFTCL_MAX_BANDS; ++bi)
-        pt[PT_CHI0B + kind * SWIFTCL_MAX_BANDS + bi] = exp(-P.fftlog_b[kind][bi] * lchi0);
   }
+  if (tid < SWIFTCL_NKINDS * SWIFTCL_MAX_BANDS)
+    P.pt[(size_t)b * PT_STRIDE + PT_CHI0B + tid] =
+        exp(-P.fftlog_b[tid / SWIFTCL_MAX_BANDS][tid % SWIFTCL_MAX_BANDS] * lchi0);
 
-  // node state: each thread owns nodes m = tid + k * nth
-  constexpr int MAXN = 2048 / GEOM_THREADS;  // n_chi <= 2048 (checked at plan time)
-  node_state ns[MAXN];
+  // zeros outside the support
   R* g = (R*)P.g;
-#pragma unroll
-  for (int k = 0; k < MAXN; ++k) {
-    const int m = tid + k * nth;
-    ns[k].active = false;
-    if (m >= N) continue;
-    if (m < m0 || m > m1) {
-      for (int t = 0; t < T; ++t)
-        for (int bi = 0; bi < nb; ++bi) {
-          g[(((size_t)b * T + t) * nb + bi) * N + m] = (R)0;
-          if (P.rsd) ((R*)P.g_r)[(((size_t)b * T + t) * nb + bi) * N + m] = (R)0;
-          if (P.mag) ((R*)P.g_mu)[(((size_t)b * T + t) * nb + bi) * N + m] = (R)0;
-        }
-      continue;
+  for (int e = tid; e < N - (m1 - m0 + 1); e += nth) {
+    const int m = e < m0 ? e : e + m1 - m0 + 1;
+    for (int r = 0; r < T * nb; ++r) {
+      g[((size_t)b * T * nb + r) * N + m] = (R)0;
+      if (P.rsd) ((R*)P.g_r)[((size_t)b * T * nb + r) * N + m] = (R)0;
+      if (P.mag) ((R*)P.g_mu)[((size_t)b * T * nb + r) * N + m] = (R)0;
     }
-    ns[k].active = true;
-    locate_node(ns[k], m, m0, m1, theta, chi0, P.delta, zg, zgih, chi, mchi, Dz, mD, nzg, zs, nzs, P.z_union, nu,
-                P.union_iv);
-    // the node geometry, for the adjoint
+  }
+  // the nodes of the support, m = m0 + tid + k nth on thread tid: their geometry, for the loops below (by
+  // the same thread) and for the adjoint
+  for (int m = m0 + tid; m <= m1; m += nth) {
+    node_state ns;
+    locate_node(ns, m, m0, m1, theta, chi0, P.delta, zg, zgih, chi, mchi, Dz, mD, nzg, zs, nzs, P.z_union, nu,
+                P.union_iv, P.union_g);
     double* nf = P.node_f + (size_t)b * 4 * N + m;
     int* ni = P.node_i + (size_t)b * 3 * N + m;
-    nf[0] = ns[k].z;
-    nf[N] = ns[k].chiz;
-    nf[2 * N] = ns[k].dchi;
-    nf[3 * N] = ns[k].D;
-    ni[0] = ns[k].ig;
-    ni[N] = ns[k].inz;
-    ni[2 * N] = ns[k].u;
+    nf[0] = ns.z;
+    nf[N] = ns.chiz;
+    nf[2 * N] = ns.dchi;
+    nf[3 * N] = ns.D;
+    ni[0] = ns.ig;
+    ni[N] = ns.inz;
+    ni[2 * N] = ns.u;
   }
   for (int g0 = 0; g0 < T; g0 += TG) {
   const int g1 = min(g0 + TG, T);
@@ -177,19 +179,31 @@ __global__ __launch_bounds__(GEOM_THREADS) void k_geometry(plan_dev P, swiftcl_i
   // clustering and CMB-lensing tracers, tracers of an unknown kind and padded slots
   const double pref = 1.5 * in.omega_m[b] * SWIFTCL_H0_OVER_C * SWIFTCL_H0_OVER_C;
   const double chis = chi[nzg - 1];  // chi_* of the CMB-lensing kernel: the top of the geometry grid
-#pragma unroll
-  for (int k = 0; k < MAXN; ++k) {
-    if (!ns[k].active) continue;
-    const int m = tid + k * nth;
+  for (int m = m0 + tid; m <= m1; m += nth) {
+    const double* nf = P.node_f + (size_t)b * 4 * N + m;
+    const int* ni = P.node_i + (size_t)b * 3 * N + m;
+    const double z = nf[0], x = nf[N], D = nf[3 * N], w = (m == m0) ? 0.5 : (m == m1 ? 0.5 + theta : 1.0);
+    const int iz = ni[N];
+    // what the tracers of a node share: the spline weights of n, w D / (dchi/dz) and the band factors
+    const spline_w nw_(zs, zsih, max(iz, 0), z);
+    const double wd = w / nf[2 * N], c0 = wd * D;
     // RSD (eq. RSD): -f(z) n dz/dchi D with f = dln D/dln a = -(1+z) D'/D, i.e. (1+z) D' n / (dchi/dz)
-    double dD = 0.0;
-    if (P.rsd) (void)spline_at(zg, zgih, Dz, mD, ns[k].ig, ns[k].z, &dD);
+    double c1 = 0.0;
+    if (P.rsd) {
+      double dD;
+      (void)spline_at(zg, zgih, Dz, mD, ni[0], z, &dD);
+      c1 = wd * (1.0 + z) * dD;
+    }
+    double eb[SWIFTCL_MAX_BANDS];
+#pragma unroll
+    for (int bi = 0; bi < SWIFTCL_MAX_BANDS; ++bi) eb[bi] = bi < nb ? P.ebm[(size_t)bi * N + m] : 0.0;
     for (int t = g0; t < g1; ++t) {
       const int kd = t < Tb ? in.kind[(size_t)b * T + t] : -1;  // -1: padded slot
+      const size_t row = ((size_t)b * T + t) * nb * N + m;      // band 0's sample
       if (kd == SWIFTCL_LENSING) {
         for (int bi = 0; bi < nb; ++bi) {
-          if (P.rsd) ((R*)P.g_r)[(((size_t)b * T + t) * nb + bi) * N + m] = (R)0;
-          if (P.mag) ((R*)P.g_mu)[(((size_t)b * T + t) * nb + bi) * N + m] = (R)0;
+          if (P.rsd) ((R*)P.g_r)[row + (size_t)bi * N] = (R)0;
+          if (P.mag) ((R*)P.g_mu)[row + (size_t)bi * N] = (R)0;
         }
         continue;
       }
@@ -197,26 +211,30 @@ __global__ __launch_bounds__(GEOM_THREADS) void k_geometry(plan_dev P, swiftcl_i
       if (t < Tb && !known && m == m0) atomicOr(P.flags, FLAG_BAD_INDEX);  // its samples stay zero
       // (the magnification samples of clustering tracers come from k_geom_lens)
       if (kd != SWIFTCL_CLUSTERING && P.mag)
-        for (int bi = 0; bi < nb; ++bi) ((R*)P.g_mu)[(((size_t)b * T + t) * nb + bi) * N + m] = (R)0;
-      double f = 0.0, fr = 0.0, w = ns[k].w;
+        for (int bi = 0; bi < nb; ++bi) ((R*)P.g_mu)[row + (size_t)bi * N] = (R)0;
       if (kd == SWIFTCL_CLUSTERING) {
-        const double n = ns[k].inz < 0 ? 0.0
-                         : spline_at(zs, zsih, nzr + (size_t)(t - g0) * nzs, mn + (size_t)(t - g0) * nzs, ns[k].inz,
-                                     ns[k].z, nullptr);
-        f = in.bias[(size_t)b * T + t] * n * ns[k].D / ns[k].dchi;
-        fr = (1.0 + ns[k].z) * dD * n / ns[k].dchi;
-      } else if (kd == SWIFTCL_CMB_LENSING) {
+        const double n =
+            iz < 0 ? 0.0 : nw_.at(nzr + (size_t)(t - g0) * nzs, mn + (size_t)(t - g0) * nzs, iz);
+        const double f = in.bias[(size_t)b * T + t] * n * c0;
+#pragma unroll
+        for (int bi = 0; bi < SWIFTCL_MAX_BANDS; ++bi) {
+          if (bi >= nb) continue;
+          g[row + (size_t)bi * N] = (R)(f * eb[bi]);
+          if (P.rsd) ((R*)P.g_r)[row + (size_t)bi * N] = (R)(n * c1 * eb[bi]);
+        }
+        continue;
+      }
+      double f = 0.0;
+      if (kd == SWIFTCL_CMB_LENSING) {
         // Sec. 2.4: one source plane at chi_*; the kernel falls linearly to zero there, so the last
         // node takes the trapezoid weight of a linear end, 1/2 + theta/2
-        const double x = ns[k].chiz;
-        f = pref * (1.0 + ns[k].z) * (chis - x) / (x * chis) * ns[k].D;
-        if (m == m1 && m1 > m0) w = 0.5 + 0.5 * theta;
+        f = pref * (1.0 + z) * (chis - x) / (x * chis) * D;
+        f *= m == m1 && m1 > m0 ? 0.5 + 0.5 * theta : w;
       }
       const int kc = known ? kd : SWIFTCL_CLUSTERING;
       for (int bi = 0; bi < nb; ++bi) {
-        g[(((size_t)b * T + t) * nb + bi) * N + m] = (R)(w * f * P.ebm[((size_t)kc * nb + bi) * N + m]);
-        if (P.rsd)
-          ((R*)P.g_r)[(((size_t)b * T + t) * nb + bi) * N + m] = (R)(w * fr * P.ebm[(size_t)bi * N + m]);
+        g[row + (size_t)bi * N] = (R)(f * P.ebm[((size_t)kc * nb + bi) * N + m]);
+        if (P.rsd) ((R*)P.g_r)[row + (size_t)bi * N] = (R)0;
       }
     }
   }

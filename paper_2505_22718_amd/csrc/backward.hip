@@ -46,9 +46,8 @@ int backward_chunks(const plan_dev& p, int batch) {
   return c < 1 ? 1 : c;
 }
 
-// Work items of the fused adjoint: item j = (rest = j / 8, XCD j % 8) is point
-// b = (rest / nchunk) * 8 + j % 8 and multipole chunk rest % nchunk (the chunks of a point share an
-// XCD's L2).  With ragged tracer and multipole counts their costs differ several-fold, and one
+// Work items of the fused adjoint: item j is the (point, multipole chunk) that xcd_item gives block j (the
+// chunks of a point share an XCD's L2).  With ragged tracer and multipole counts their costs differ several-fold, and one
 // 1024-thread workgroup fills a CU, so the workgroups are dispatched heaviest first (longest
 // processing time first keeps the last CUs from idling): k_bwd_order writes order[w] = the item of
 // workgroup w, a stable counting sort on a cost bucket of T_b x (multipoles of the chunk), so
@@ -69,8 +68,8 @@ __global__ __launch_bounds__(1024) void k_bwd_order(plan_dev P, swiftcl_inputs i
       const int j = 4 * w + q;
       int key = 255;
       if (j < n) {
-        const int rest = j / SWIFTCL_NXCD, chunk = rest % nchunk;
-        const int b = (rest / nchunk) * SWIFTCL_NXCD + j % SWIFTCL_NXCD;
+        int b, chunk;
+        xcd_item(j, in.batch, nchunk, &b, &chunk);
         key = 63;
         if (b < in.batch) {
           const int Tb = clampb(in.n_tracers[b], 0, T), Lb = clampb(in.n_ell[b], 0, Lm);
@@ -158,10 +157,8 @@ __global__ __launch_bounds__(NW * 64) void k_bwd_windows(plan_dev P, swiftcl_inp
   __shared__ R Gp[4][64];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / SWIFTCL_WAVE), lane = threadIdx.x % SWIFTCL_WAVE;
   const int item = ordered ? P.bwd_order[blockIdx.x] : (int)blockIdx.x;
-  const int xcd = item % SWIFTCL_NXCD;
-  const int rest = item / SWIFTCL_NXCD;
-  const int chunk = rest % nchunk;
-  const int b = (rest / nchunk) * SWIFTCL_NXCD + xcd;
+  int b, chunk;
+  xcd_item(item, in.batch, nchunk, &b, &chunk);
   if (b >= in.batch) return;
   const int Tb = clampb(in.n_tracers[b], 0, T);
   const int Lb = clampb(in.n_ell[b], 0, Lm);
@@ -797,23 +794,26 @@ __global__ __launch_bounds__(256) void k_bwd_adj(plan_dev P, swiftcl_inputs in, 
 }
 
 // Reduce dc over chunks and take it back through the forward real transform: dg per
-// (point, tracer, band), one wavefront per row.
-template <typename R, int M>
+// (point, tracer, band).  WPR 1: one wavefront per row, four rows per workgroup.  WPR 4: the four
+// wavefronts of a workgroup share the chunk sums of one row, 8 chunks' loads in flight, and the first
+// one transforms (launches of many chunks, few points: 103 chunks of one point took 38 us with one
+// wavefront per row, a load latency per chunk).  Every entry adds its chunks in order, in both.
+template <typename R, int M, int WPR>
 __global__ __launch_bounds__(256) void k_bwd_coeffs(plan_dev P, swiftcl_inputs in, int nchunk) {
-  __shared__ C2<R> lds[4][fft_lds_size(M, sizeof(R))];
+  __shared__ C2<R> lds[WPR == 1 ? 4 : 1][fft_lds_size(M, sizeof(R))];
   // FP32: the twiddle table staged in LDS by the block (FP64 reads it through the cache)
   constexpr bool TWS = sizeof(R) == 4;
   __shared__ C2<R> stw_s[TWS ? 2 * M : 1];
   if constexpr (TWS) {
     for (int i = threadIdx.x; i < 2 * M; i += blockDim.x) stw_s[i] = ((const C2<R>*)P.tw)[i];
-    __syncthreads();
+    if (WPR == 1) __syncthreads();
   }
   const C2<R>* twp = TWS ? (const C2<R>*)stw_s : (const C2<R>*)P.tw;
   constexpr int RL = M / SWIFTCL_WAVE;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / SWIFTCL_WAVE), lane = threadIdx.x % SWIFTCL_WAVE;
   const int T = P.max_tracers, nb = P.n_bands, N = P.N;
   const long rows = (long)in.batch * T * nb;
-  const long row = (long)blockIdx.x * 4 + wave;
+  const long row = WPR == 1 ? (long)blockIdx.x * 4 + wave : (long)blockIdx.x;
   if (row >= rows) return;
   const int bi = (int)(row % nb);
   const int t = (int)((row / nb) % T);
@@ -821,17 +821,40 @@ __global__ __launch_bounds__(256) void k_bwd_coeffs(plan_dev P, swiftcl_inputs i
   C2<R>* out = (C2<R>*)((R*)P.dg + row * N);
   const int Tb = clampb(in.n_tracers[b], 0, T);
   if (t >= Tb) {
+    if (WPR == 1 || wave == 0)
 #pragma unroll
-    for (int e = 0; e < RL; ++e) out[lane + SWIFTCL_WAVE * e] = mk<R>(0, 0);
+      for (int e = 0; e < RL; ++e) out[lane + SWIFTCL_WAVE * e] = mk<R>(0, 0);
     return;
   }
+  const size_t stride = (size_t)T * nb * M;  // chunk stride of the partial rows
+  const C2<R>* src = (const C2<R>*)P.dchat_part + (((size_t)b * nchunk * T + t) * nb + bi) * M;
   C2<R> v[RL];
+  if constexpr (WPR == 1) {
 #pragma unroll
-  for (int e = 0; e < RL; ++e) v[e] = mk<R>(0, 0);
-  for (int c = 0; c < nchunk; ++c) {
-    const C2<R>* src = (const C2<R>*)P.dchat_part + ((((size_t)b * nchunk + c) * T + t) * nb + bi) * M;
+    for (int e = 0; e < RL; ++e) v[e] = mk<R>(0, 0);
+    for (int c = 0; c < nchunk; ++c) {
 #pragma unroll
-    for (int e = 0; e < RL; ++e) v[e] = cadd(v[e], src[lane + SWIFTCL_WAVE * e]);
+      for (int e = 0; e < RL; ++e) v[e] = cadd(v[e], src[c * stride + lane + SWIFTCL_WAVE * e]);
+    }
+  } else {
+    __shared__ C2<R> sum[M];
+    for (int n = threadIdx.x; n < M; n += 256) {
+      C2<R> a = mk<R>(0, 0);
+      int c = 0;
+      for (; c + 8 <= nchunk; c += 8) {
+        C2<R> x[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) x[q] = src[(c + q) * stride + n];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) a = cadd(a, x[q]);
+      }
+      for (; c < nchunk; ++c) a = cadd(a, src[c * stride + n]);
+      sum[n] = a;
+    }
+    __syncthreads();
+    if (wave != 0) return;
+#pragma unroll
+    for (int e = 0; e < RL; ++e) v[e] = sum[lane + SWIFTCL_WAVE * e];
   }
   const double* pt = P.pt + (size_t)b * PT_STRIDE;
   const int kind = tracer_kind(in, T, b, t);
@@ -845,9 +868,21 @@ __global__ __launch_bounds__(256) void k_bwd_coeffs(plan_dev P, swiftcl_inputs i
     C2<R> en = cmul(v[e], mk<R>((R)(cs * scale), (R)(-sn * scale)));
     v[e] = n == 0 ? en : cscale(en, (R)0.5);
   }
-  wave_c2r<R, M>(v, lds[wave], twp, lane);
+  wave_c2r<R, M>(v, lds[WPR == 1 ? wave : 0], twp, lane);
 #pragma unroll
   for (int e = 0; e < RL; ++e) out[lane + SWIFTCL_WAVE * e] = v[e];
+}
+
+// The chunk sums share a row between four wavefronts where the chunks are many and the rows too few to fill
+// the chip (23 points of 12 tracers, 12 chunks, 828 rows: 8.0 -> 7.6 us; 5760 rows of 14 chunks: 143 -> 181 us).
+template <typename R, int M>
+static hipError_t launch_bwd_coeffs(const plan_dev& p, const swiftcl_inputs* in, int nchunk, hipStream_t s) {
+  const long rows = (long)in->batch * p.max_tracers * p.n_bands;
+  if (nchunk >= 8 && rows <= 4 * p.persist_blocks)
+    hipLaunchKernelGGL((k_bwd_coeffs<R, M, 4>), dim3((unsigned)rows), dim3(256), 0, s, p, *in, nchunk);
+  else
+    hipLaunchKernelGGL((k_bwd_coeffs<R, M, 1>), dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, p, *in, nchunk);
+  return hipGetLastError();
 }
 
 size_t bwd_geometry_lds_bytes(const plan_dev& p) {
@@ -900,6 +935,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(6))) void k
   double* seg0 = mt + nzs;               // [nu]
   double* seg1 = seg0 + nu;              // [nu]
   double* tmp = seg1 + nu;               // [64]
+  double* scan = tmp;                    // (32 of them, once the bias sum is read)
 
   const int kd = in.kind[(size_t)b * T + t];
   const int kind = tracer_kind(in, T, b, t);  // a tracer of an unknown kind has no cotangent below
@@ -1051,9 +1087,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(6))) void k
     for (int w = 0; w < nth / SWIFTCL_WAVE; ++w) s += tmp[w];
     dbias[(size_t)b * T + t] = kd == SWIFTCL_CLUSTERING ? s : 0.0;
   }
-  // n spline transpose
-  if (wave == 0) wave_spline_adjoint(dny, dnM, P.lu_nz, nzs, lane);
-  __syncthreads();
+  // n spline transpose (the scan's space is that of the bias sum, which thread 0 reads before its first barrier)
+  block_spline_adjoint(dny, dnM, P.lu_nz, nzs, scan);
   if (dnz)
     for (int i = tid; i < nzs; i += nth) dnz[((size_t)b * T + t) * nzs + i] = dny[i];
   double* part = P.ddD_part + ((size_t)b * T + t) * 2 * nzg;
@@ -1073,9 +1108,13 @@ static hipError_t launch_bwd_tracer(const plan_dev& p, const swiftcl_inputs* in,
   return hipGetLastError();
 }
 
-// Per point: dL/dP (the chunk partials times (2/pi) w k^3) and dL/dD (the tracers' shares summed
-// in tracer order, then the D spline transpose), one workgroup of 1024 threads (FP64): one
-// geometry sample per thread, its tracer loads issued together.
+// Per point, workgroups of 1024 threads (FP64).  Block y = 0: dL/dD (the tracers' shares summed in tracer
+// order, then the D spline transpose), one geometry sample per thread, its tracer loads issued together.
+// dL/dP is the chunk partials times (2/pi) w k^3: by block y = 0 after that where the chunks are few, else
+// by the blocks y >= 1, 128 k nodes each, 8 threads per node taking every 8th chunk (103 chunks of one point
+// by one thread per node took 40 us).
+constexpr int BWD_PK_K = 128;
+
 template <typename R>
 __global__ __launch_bounds__(1024) void k_bwd_point(plan_dev P, swiftcl_inputs in, int nchunk, double* dpk,
                                                      double* dD) {
@@ -1083,12 +1122,28 @@ __global__ __launch_bounds__(1024) void k_bwd_point(plan_dev P, swiftcl_inputs i
   const int b = blockIdx.x;
   if (b >= in.batch) return;
   const int tid = threadIdx.x, nth = blockDim.x;
-  const int wave = tid / SWIFTCL_WAVE, lane = tid % SWIFTCL_WAVE;
   const int T = P.max_tracers, nzg = P.n_zg, nk = P.n_k;
-  if (dpk) {
+  const R* pp = (const R*)P.dpk_part + (size_t)b * nchunk * nk;
+  if (blockIdx.y > 0) {
+    __shared__ double part[1024];
+    const int k = (blockIdx.y - 1) * BWD_PK_K + tid % BWD_PK_K;
+    double s = 0.0;
+    if (k < nk) {
+#pragma unroll 4
+      for (int c = tid / BWD_PK_K; c < nchunk; c += 1024 / BWD_PK_K) s += (double)pp[(size_t)c * nk + k];
+    }
+    part[tid] = s;
+    __syncthreads();
+    if (tid < BWD_PK_K && k < nk) {
+      for (int q = 1; q < 1024 / BWD_PK_K; ++q) s += part[q * BWD_PK_K + tid];
+      dpk[(size_t)b * nk + k] = P.kw[k] * s;
+    }
+    return;
+  }
+  if (dpk && gridDim.y == 1) {
     for (int k = tid; k < nk; k += nth) {
       double s = 0.0;
-      for (int c = 0; c < nchunk; ++c) s += (double)((const R*)P.dpk_part)[((size_t)b * nchunk + c) * nk + k];
+      for (int c = 0; c < nchunk; ++c) s += (double)pp[(size_t)c * nk + k];
       dpk[(size_t)b * nk + k] = P.kw[k] * s;
     }
   }
@@ -1108,9 +1163,18 @@ __global__ __launch_bounds__(1024) void k_bwd_point(plan_dev P, swiftcl_inputs i
     dDM[i] = sm;
   }
   __syncthreads();
-  if (wave == 0) wave_spline_adjoint(dDy, dDM, P.lu_geom, nzg, lane);
-  __syncthreads();
+  __shared__ double scan[block_scan_doubles(1, 1024)];
+  block_spline_adjoint(dDy, dDM, P.lu_geom, nzg, scan);
   for (int i = tid; i < nzg; i += nth) dD[(size_t)b * nzg + i] = dDy[i];
+}
+
+template <typename R>
+static hipError_t launch_bwd_point(const plan_dev& p, const swiftcl_inputs* in, int nchunk, double* dpk, double* dD,
+                                   hipStream_t s) {
+  const int ny = dpk && nchunk >= 8 ? 1 + (p.n_k + BWD_PK_K - 1) / BWD_PK_K : 1;
+  hipLaunchKernelGGL(k_bwd_point<R>, dim3(in->batch, ny), dim3(1024), 2 * (size_t)p.n_zg * sizeof(double), s, p, *in,
+                     nchunk, dpk, dD);
+  return hipGetLastError();
 }
 
 size_t bwd_windows_lds(const plan_dev& p) {
@@ -1131,9 +1195,9 @@ static hipError_t launch_bwd_t(const plan_dev& p, const swiftcl_inputs* in, cons
   const bool pack = !dp && p.bwd_pack && p.bwd_chunk_mul <= 4;
   auto k1 = pack ? k_bwd_windows<R, M, NW, TW, !dp> : k_bwd_windows<R, M, NW, TW>;
   hipError_t e;
-  const size_t groups = (size_t)(in->batch + SWIFTCL_NXCD - 1) / SWIFTCL_NXCD;
-  const long n = (long)groups * nchunk * SWIFTCL_NXCD;
-  const int ordered = p.bwd_order && n <= p.bwd_order_n && n <= BWD_ORDER_MAX;
+  const long n = (long)xcd_blocks(in->batch, nchunk);
+  // (no order where every workgroup has a compute unit to itself: one more launch, 5 us, for nothing)
+  const int ordered = p.bwd_order && n > p.persist_blocks && n <= p.bwd_order_n && n <= BWD_ORDER_MAX;
   if (ordered) {
     hipLaunchKernelGGL(k_bwd_order, dim3(1), dim3(1024), 0, s, p, *in, nchunk, (int)n);
     if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -1141,15 +1205,10 @@ static hipError_t launch_bwd_t(const plan_dev& p, const swiftcl_inputs* in, cons
   hipLaunchKernelGGL(k1, dim3((unsigned)n), dim3(NW * 64), lds, s, p, *in, (const R*)dC, nchunk, ordered);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (ev && (e = hipEventRecord(ev[0], s)) != hipSuccess) return e;
-  const long rows = (long)in->batch * p.max_tracers * p.n_bands;
-  hipLaunchKernelGGL((k_bwd_coeffs<R, M>), dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, p, *in,
-                     pack ? 2 * nchunk : nchunk);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
+  if ((e = launch_bwd_coeffs<R, M>(p, in, pack ? 2 * nchunk : nchunk, s)) != hipSuccess) return e;
   if (ev && (e = hipEventRecord(ev[1], s)) != hipSuccess) return e;
   if ((dbias || dnz || dD) && (e = launch_bwd_tracer<R>(p, in, dbias, dnz, s)) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_bwd_point<R>, dim3(in->batch), dim3(1024), 2 * (size_t)p.n_zg * sizeof(double), s, p, *in,
-                     nchunk, dpk, dD);
-  return hipGetLastError();
+  return launch_bwd_point<R>(p, in, nchunk, dpk, dD, s);
 }
 
 template <typename R>
@@ -1159,10 +1218,7 @@ static hipError_t launch_chain_t(const plan_dev& p, const swiftcl_inputs* in, do
     hipError_t e = launch_bwd_tracer<R>(p, in, dbias, dnz, s);
     if (e != hipSuccess) return e;
   }
-  if (dD)
-    hipLaunchKernelGGL(k_bwd_point<R>, dim3(in->batch), dim3(1024), 2 * (size_t)p.n_zg * sizeof(double), s, p, *in,
-                       0, nullptr, dD);
-  return hipGetLastError();
+  return dD ? launch_bwd_point<R>(p, in, 0, nullptr, dD, s) : hipSuccess;
 }
 
 hipError_t launch_bwd_chain(const plan_dev& p, const swiftcl_inputs* in, double* dbias, double* dnz, double* dD,
@@ -1189,9 +1245,7 @@ hipError_t launch_bwd_gv(const plan_dev& p, const swiftcl_inputs* in, const void
 
 // dL/dP from the partials of launch_bwd_gv (every point of the batch)
 hipError_t launch_bwd_dpk(const plan_dev& p, const swiftcl_inputs* in, double* dpk, hipStream_t s) {
-  hipLaunchKernelGGL(k_bwd_point<float>, dim3(in->batch), dim3(1024), 2 * (size_t)p.n_zg * sizeof(double), s, p, *in,
-                     p.bwd_nlc, dpk, nullptr);
-  return hipGetLastError();
+  return launch_bwd_point<float>(p, in, p.bwd_nlc, dpk, nullptr, s);
 }
 
 // The adjoint through the workspace (FP32; plans with adjoint == 2)
@@ -1210,14 +1264,10 @@ static hipError_t launch_bwd_ws(const plan_dev& p, const swiftcl_inputs* in, con
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   if (ev && (e = hipEventRecord(ev[0], s)) != hipSuccess) return e;
-  const long rows = (long)in->batch * T * p.n_bands;
-  hipLaunchKernelGGL((k_bwd_coeffs<float, M>), dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, p, *in, nlc);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
+  if ((e = launch_bwd_coeffs<float, M>(p, in, nlc, s)) != hipSuccess) return e;
   if (ev && (e = hipEventRecord(ev[1], s)) != hipSuccess) return e;
   if ((dbias || dnz || dD) && (e = launch_bwd_tracer<float>(p, in, dbias, dnz, s)) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_bwd_point<float>, dim3(in->batch), dim3(1024), 2 * (size_t)p.n_zg * sizeof(double), s, p, *in,
-                     nlc, dpk, dD);
-  return hipGetLastError();
+  return launch_bwd_point<float>(p, in, nlc, dpk, dD, s);
 }
 
 hipError_t launch_backward(const plan_dev& p, const swiftcl_inputs* in, const void* dC, double* dpk, double* dbias,

@@ -275,9 +275,8 @@ __device__ __forceinline__ void windows_cl_item(const plan_dev& P, const swiftcl
   }
 }
 
-// Launch modes.  MODE 0: one workgroup per (point, multipole slot), blocks mapped so that all
-// multipoles of one point run on one XCD (block = ((b / 8) * Lm + l) * 8 + b % 8); padded slots
-// write zeros.  MODE 1: a grid sized to the chip; the blocks of XCD x walk the compact list of
+// Launch modes.  MODE 0: one workgroup per (point, multipole slot), mapped to the XCDs by xcd_item;
+// padded slots write zeros.  MODE 1: a grid sized to the chip; the blocks of XCD x walk the compact list of
 // (point b = 8 i + x, multipole) items built by k_schedule with the grid stride (ragged multipole
 // counts leave no idle workgroup, and every block loads the twiddles once).  MODE 2: as MODE 1 over
 // the packed list of k_schedule_packed, whose tasks hold one or two items of the XCD's points with
@@ -299,8 +298,8 @@ __attribute__((amdgpu_waves_per_eu((sizeof(R) == 4 && DO_CL && M <= 512) ? 8 : 1
   const int rest = blockIdx.x / SWIFTCL_NXCD;
   const C2<R>* stw = TW_LDS ? stw_l : (const C2<R>*)P.tw;
   if constexpr (MODE == 0) {
-    const int li = rest % P.max_ell;
-    const int b = (rest / P.max_ell) * SWIFTCL_NXCD + xcd;
+    int b, li;
+    xcd_item(blockIdx.x, in.batch, P.max_ell, &b, &li);
     if (b >= in.batch) return;
     if constexpr (TW_LDS) {
       const C2<R>* gtw = (const C2<R>*)P.tw;
@@ -522,10 +521,8 @@ __global__ __launch_bounds__(NW * 64) void k_windows_v(plan_dev P, swiftcl_input
   C2<R>* fbuf = stw_l + NTW;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / SWIFTCL_WAVE), lane = threadIdx.x % SWIFTCL_WAVE;
   const int T = P.max_tracers, Lm = P.max_ell, nk = P.n_k, nb = P.n_bands;
-  const int xcd = blockIdx.x % SWIFTCL_NXCD;
-  const int rest = blockIdx.x / SWIFTCL_NXCD;
-  const int li = rest % Lm;
-  const int bl = (rest / Lm) * SWIFTCL_NXCD + xcd;
+  int bl, li;
+  xcd_item(blockIdx.x, nbp, Lm, &bl, &li);
   if (bl >= nbp) return;
   const int b = b0 + bl;
   const int Tb = clampi(in.n_tracers[b], 0, T);
@@ -772,8 +769,7 @@ static hipError_t launch_unfused(const plan_dev& p, const swiftcl_inputs* in, vo
   const size_t lds = windows_cl_lds(M, NW, TW, false, sizeof(float), p.n_k);
   for (int b0 = 0; b0 < in->batch; b0 += p.vchunk) {
     const int nbp = in->batch - b0 < p.vchunk ? in->batch - b0 : p.vchunk;
-    const size_t groups = (size_t)(nbp + SWIFTCL_NXCD - 1) / SWIFTCL_NXCD;
-    const dim3 g1((unsigned)(groups * p.max_ell * SWIFTCL_NXCD));
+    const dim3 g1(xcd_blocks(nbp, p.max_ell));
 #define SWIFTCL_WV(SP, EX) hipLaunchKernelGGL((k_windows_v<M, NW, TW, SP, EX>), g1, dim3(NW * 64), lds, s, p, *in, b0, nbp, 0)
     switch ((p.rsd ? 1 : 0) | (p.mag ? 2 : 0)) {
       case 0: if (split) SWIFTCL_WV(true, 0); else SWIFTCL_WV(false, 0); break;
@@ -797,8 +793,7 @@ static hipError_t launch_ww_t(const plan_dev& p, const swiftcl_inputs* in, int b
   constexpr int NW = 16;
   constexpr bool TW = unfused_tw(M);
   const size_t lds = windows_cl_lds(M, NW, TW, false, sizeof(float), p.n_k);
-  const size_t groups = (size_t)(nbp + SWIFTCL_NXCD - 1) / SWIFTCL_NXCD;
-  const dim3 g1((unsigned)(groups * p.max_ell * SWIFTCL_NXCD));
+  const dim3 g1(xcd_blocks(nbp, p.max_ell));
   // the recomputed W carries the RSD and magnification terms of plans built with them
   switch ((p.rsd ? 1 : 0) | (p.mag ? 2 : 0)) {
     case 0: hipLaunchKernelGGL((k_windows_v<M, NW, TW, false, 0>), g1, dim3(NW * 64), lds, s, p, *in, b0, nbp, 1); break;
@@ -861,8 +856,7 @@ static hipError_t launch_wcl_t(const plan_dev& p, const swiftcl_inputs* in, void
                        (R*)W, (R*)C);
     return hipGetLastError();
   }
-  const size_t groups = (size_t)(in->batch + SWIFTCL_NXCD - 1) / SWIFTCL_NXCD;
-  const dim3 grid((unsigned)(groups * p.max_ell * SWIFTCL_NXCD));
+  const dim3 grid(xcd_blocks(in->batch, p.max_ell));
   if constexpr (sizeof(R) == 4 && DO_CL) {
     if (split) {
       hipLaunchKernelGGL((k_windows_cl<R, M, NW, TW, WRITE_W, DO_CL, 0, true>), grid, dim3(NW * 64), lds, s, p,

@@ -122,8 +122,12 @@ __global__ __launch_bounds__(256) void k_kg_fft(plan_dev P, swiftcl_inputs in, c
   }
   if (bad) atomicOr(P.flags, FLAG_NONFINITE);
   __syncthreads();
-  if (wave == 0) wave_spline(y, P.lu_geom, nzg, Mo, lane);
-  __syncthreads();
+  {
+    __shared__ double scan[block_scan_doubles(1, 256)];
+    const double* const ys[1] = {y};
+    double* const ms[1] = {Mo};
+    block_spline<1>(ys, P.lu_geom, nzg, ms, scan);
+  }
   // growth of node a at every active chi node (zero outside the support, where g is zero)
   const double* pt = P.pt + (size_t)b * PT_STRIDE;
   const int m0 = P.m0, m1 = (int)pt[PT_M1];

@@ -35,27 +35,26 @@ namespace {
 
 __device__ __forceinline__ int clamp_i(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
 
-// Growth at the nodes: one wavefront per (point, node); its spline moments in LDS [4][n_zg].  Bound by
-// the latency of the two spline sweeps (four wavefronts per workgroup keep up to 20 splines on a CU).
+// Growth at the nodes: one workgroup per (point, node); its spline moments in LDS [n_zg].
 __global__ __launch_bounds__(256) void k_kc_dz(plan_dev P, swiftcl_inputs in, const double* __restrict__ Dkz, int b0,
                                                int nbp) {
-  extern __shared__ double sh[];
+  extern __shared__ double Mo[];
+  __shared__ double scan[block_scan_doubles(1, 256)];
   const int nzg = P.n_zg, A = P.n_interp, N = P.N, NS = P.kc_ns;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / SWIFTCL_WAVE), lane = threadIdx.x % SWIFTCL_WAVE;
-  const int ga = (A + 3) / 4;
-  const int bl = blockIdx.x / ga, a = (blockIdx.x % ga) * 4 + wave;
-  if (bl >= nbp || a >= A) return;  // whole wavefronts leave; no block barrier below
+  const int bl = blockIdx.x / A, a = blockIdx.x % A;
+  if (bl >= nbp) return;
   const int b = b0 + bl;
-  double* Mo = sh + (size_t)wave * nzg;
   const double* y = Dkz + ((size_t)b * A + a) * nzg;
   bool bad = false;
-  for (int i = lane; i < nzg; i += SWIFTCL_WAVE) bad |= !isfinite(y[i]);
+  for (int i = threadIdx.x; i < nzg; i += blockDim.x) bad |= !isfinite(y[i]);
   if (bad) atomicOr(P.flags, FLAG_NONFINITE);
-  wave_spline(y, P.lu_geom, nzg, Mo, lane);
+  const double* const ys[1] = {y};
+  double* const ms[1] = {Mo};
+  block_spline<1>(ys, P.lu_geom, nzg, ms, scan);
   const int m0 = P.m0, m1 = (int)P.pt[(size_t)b * PT_STRIDE + PT_M1];
   const double* zgih = P.lu_geom + 3 * (size_t)nzg;
   double* out = P.kc_dn + ((size_t)bl * A + a) * NS;
-  for (int m = m0 + lane; m <= m1; m += SWIFTCL_WAVE) {
+  for (int m = m0 + threadIdx.x; m <= m1; m += blockDim.x) {
     const int ig = P.node_i[(size_t)b * 3 * N + m];
     out[m - m0] = spline_w(P.z_geom, zgih, ig, P.node_f[(size_t)b * 4 * N + m]).at(y, Mo, ig);
   }
@@ -415,8 +414,8 @@ hipError_t launch_kc_rows(const plan_dev& p, const swiftcl_inputs* in, const dou
   const int T = p.max_tracers, A = p.n_interp;
   const double h = (double)(p.n_k - 1) * p.delta / (double)(A - 1);
   const int NJ = (p.n_k + KC_J - 1) / KC_J;
-  hipLaunchKernelGGL(k_kc_dz, dim3((unsigned)((size_t)nbp * ((A + 3) / 4))), dim3(256),
-                     (size_t)4 * p.n_zg * sizeof(double), s, p, *in, D_kz, b0, nbp);
+  hipLaunchKernelGGL(k_kc_dz, dim3((unsigned)((size_t)nbp * A)), dim3(256), (size_t)p.n_zg * sizeof(double), s, p,
+                     *in, D_kz, b0, nbp);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_kc_dk, dim3((p.kc_ns + 63) / 64, nbp), dim3(64), 0, s, p, b0, nbp, 6.0 / (h * h));

@@ -16,7 +16,7 @@ namespace {
 
 __device__ __forceinline__ int clamp_l(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
 
-// ln P and its natural-spline moments in ln k: one block per point, the spline by its first wavefront.
+// ln P and its natural-spline moments in ln k: one block per point.
 __global__ __launch_bounds__(512) void k_limber_pk(plan_dev P, swiftcl_inputs in) {
   extern __shared__ double sh[];
   const int b = blockIdx.x, nk = P.n_k;
@@ -30,8 +30,10 @@ __global__ __launch_bounds__(512) void k_limber_pk(plan_dev P, swiftcl_inputs in
   }
   if (bad) atomicOr(P.flags, FLAG_NONFINITE);
   __syncthreads();
-  if (threadIdx.x < SWIFTCL_WAVE) wave_spline(y, P.lu_k, nk, Mo, threadIdx.x);
-  __syncthreads();
+  __shared__ double scan[block_scan_doubles(1, 512)];
+  const double* const ys[1] = {y};
+  double* const ms[1] = {Mo};
+  block_spline<1>(ys, P.lu_k, nk, ms, scan);
   for (int j = threadIdx.x; j < nk; j += blockDim.x) {
     P.lnp[((size_t)b * 2) * nk + j] = y[j];
     P.lnp[((size_t)b * 2 + 1) * nk + j] = Mo[j];
@@ -392,20 +394,19 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NT == 1 ? 4
   }
 }
 
-// dL/dP per point: the moments' cotangents through the spline solve, then ln P -> P.  One
-// wavefront per point.
-__global__ __launch_bounds__(64) void k_limber_bwd_pk(plan_dev P, swiftcl_inputs in, double* dpk) {
+// dL/dP per point: the moments' cotangents through the spline solve, then ln P -> P.
+__global__ __launch_bounds__(512) void k_limber_bwd_pk(plan_dev P, swiftcl_inputs in, double* dpk) {
   extern __shared__ double sh[];
-  const int b = blockIdx.x, lane = threadIdx.x, nk = P.n_k;
+  __shared__ double scan[block_scan_doubles(1, 512)];
+  const int b = blockIdx.x, nk = P.n_k;
   double* dy = sh;
   double* dM = sh + nk;
-  for (int j = lane; j < nk; j += SWIFTCL_WAVE) {
+  for (int j = threadIdx.x; j < nk; j += blockDim.x) {
     dy[j] = P.lim_acc[((size_t)b * 2) * nk + j];
     dM[j] = P.lim_acc[((size_t)b * 2 + 1) * nk + j];
   }
-  wave_sync();
-  wave_spline_adjoint(dy, dM, P.lu_k, nk, lane);
-  for (int j = lane; j < nk; j += SWIFTCL_WAVE) {
+  block_spline_adjoint(dy, dM, P.lu_k, nk, scan);
+  for (int j = threadIdx.x; j < nk; j += blockDim.x) {
     const double v = in.pk[(size_t)b * nk + j];
     // ln P is taken of max(P, 1e-300): no gradient below that floor
     dpk[(size_t)b * nk + j] = v > 1e-300 ? dy[j] / v : 0.0;
@@ -463,7 +464,7 @@ hipError_t launch_limber_backward(const plan_dev& p, const swiftcl_inputs* in, c
   }
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (dpk) {
-    hipLaunchKernelGGL(k_limber_bwd_pk, dim3(in->batch), dim3(64), sizeof(double) * 2 * (size_t)p.n_k, s, p, *in,
+    hipLaunchKernelGGL(k_limber_bwd_pk, dim3(in->batch), dim3(512), sizeof(double) * 2 * (size_t)p.n_k, s, p, *in,
                        dpk);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }

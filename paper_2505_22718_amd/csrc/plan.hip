@@ -328,7 +328,7 @@ static void free_plan(swiftcl_plan_s* p) {
   if (!p) return;
   void* ptrs[] = {p->d.U, p->d.kscale, p->d.tw, p->d.fell, p->d.ell_band, p->d.kw, p->d.ell_v, p->d.lnk, p->d.lu_k,
                   p->d.lnp, p->d.lim_acc, p->d.ebm, p->d.z_geom, p->d.z_nz, p->d.lu_geom,
-                  p->d.lu_nz, p->d.z_union, p->d.union_iv, p->d.pt, p->d.m_chi, p->d.m_D, p->d.m_ia, p->d.m_n, p->d.lens_q, p->d.phase, p->d.node_f, p->d.node_i, p->d.ddD_part, p->d.g,
+                  p->d.lu_nz, p->d.z_union, p->d.union_iv, p->d.union_g, p->d.pt, p->d.m_chi, p->d.m_D, p->d.m_ia, p->d.m_n, p->d.lens_q, p->d.phase, p->d.node_f, p->d.node_i, p->d.ddD_part, p->d.g,
                   p->d.chat, p->d.sqrt_s, p->d.kss, p->d.flags, p->d.dchat_part, p->d.dpk_part, p->d.dg, p->d.sched, p->d.bwd_order, p->d.vbuf,
                   p->d.kg_ones, p->d.kg_ia, p->d.kg_w, p->d.kg_ip, p->d.kg_uh, p->d.kg_c, p->d.kg_m, p->d.kg_perm,
                   p->d.kg_tile, p->d.kc_w, p->d.kc_ip, p->d.kc_u, p->d.kc_tw, p->d.kc_dn, p->d.kc_dm, p->d.kc_dt,
@@ -501,6 +501,10 @@ extern "C" swiftcl_status swiftcl_plan(const swiftcl_plan_desc* d, void* stream,
     uiv[p->d.n_union + u] = in;
   }
 
+  // position of every geometry sample among the knots
+  std::vector<int> ug(d->n_zg);
+  for (int i = 0; i < d->n_zg; ++i) ug[i] = (int)(std::lower_bound(zu.begin(), zu.end(), d->z_geom[i]) - zu.begin());
+
   // --- device allocations ---
 #define ALLOC(ptr, type, count)                                             \
   do {                                                                      \
@@ -528,6 +532,7 @@ extern "C" swiftcl_status swiftcl_plan(const swiftcl_plan_desc* d, void* stream,
   ALLOC(lu_nz, double, lun.size());
   ALLOC(z_union, double, zu.size());
   ALLOC(union_iv, int, uiv.size());
+  ALLOC(union_g, int, ug.size());
   ALLOC(pt, double, (size_t)B * PT_STRIDE);
   ALLOC(m_chi, double, (size_t)B * p->d.n_zg);
   ALLOC(m_D, double, (size_t)B * p->d.n_zg);
@@ -689,6 +694,7 @@ extern "C" swiftcl_status swiftcl_plan(const swiftcl_plan_desc* d, void* stream,
       {p->d.lu_nz, lun.data(), lun.size() * sizeof(double)},
       {p->d.z_union, zu.data(), zu.size() * sizeof(double)},
       {p->d.union_iv, uiv.data(), uiv.size() * sizeof(int)},
+      {p->d.union_g, ug.data(), ug.size() * sizeof(int)},
       {d_ell, d->ell, (size_t)p->d.n_ell * sizeof(double)},
   };
   for (auto& u : ups) {

@@ -47,6 +47,10 @@ __global__ __launch_bounds__(GEOM_THREADS) void k_geometry(plan_dev P, swiftcl_i
     if (tid == 0) atomicOr(P.flags, FLAG_BAD_INDEX);
     Tb = Tb < 1 ? 0 : T;
   }
+  // kind and bias of tracer t sit in lane t of every wavefront (<= 32 tracers): the loops over the tracers
+  // read them without a load
+  const int kd_l = lane < Tb ? in.kind[(size_t)b * T + lane] : -1;  // -1: padded slot
+  const double bias_l = lane < Tb ? in.bias[(size_t)b * T + lane] : 0.0;
   // LDS layout
   double* zg = sh;                      // [nzg] geometry grid
   double* zgih = zg + nzg;              // [nzg] 1/h
@@ -198,7 +202,7 @@ __global__ __launch_bounds__(GEOM_THREADS) void k_geometry(plan_dev P, swiftcl_i
 #pragma unroll
     for (int bi = 0; bi < SWIFTCL_MAX_BANDS; ++bi) eb[bi] = bi < nb ? P.ebm[(size_t)bi * N + m] : 0.0;
     for (int t = g0; t < g1; ++t) {
-      const int kd = t < Tb ? in.kind[(size_t)b * T + t] : -1;  // -1: padded slot
+      const int kd = __builtin_amdgcn_readlane(kd_l, t);
       const size_t row = ((size_t)b * T + t) * nb * N + m;      // band 0's sample
       if (kd == SWIFTCL_LENSING) {
         for (int bi = 0; bi < nb; ++bi) {
@@ -215,7 +219,7 @@ __global__ __launch_bounds__(GEOM_THREADS) void k_geometry(plan_dev P, swiftcl_i
       if (kd == SWIFTCL_CLUSTERING) {
         const double n =
             iz < 0 ? 0.0 : nw_.at(nzr + (size_t)(t - g0) * nzs, mn + (size_t)(t - g0) * nzs, iz);
-        const double f = in.bias[(size_t)b * T + t] * n * c0;
+        const double f = readlane_f64(bias_l, t) * n * c0;
 #pragma unroll
         for (int bi = 0; bi < SWIFTCL_MAX_BANDS; ++bi) {
           if (bi >= nb) continue;

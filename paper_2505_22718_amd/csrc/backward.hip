@@ -178,7 +178,7 @@ __global__ __launch_bounds__(NW * 64) void k_bwd_windows(plan_dev P, swiftcl_inp
   }
   const size_t slot = (size_t)b * nchunk + chunk;
   C2<R>* part = (C2<R>*)P.dchat_part + slot * (PACK ? 2 : 1) * T * nb * M;
-  if (!COMPACT)  // (COMPACT: every (tracer, band) row of the slot is stored once, below)
+  if (!COMPACT)  // (COMPACT: every (tracer, band) row that the chunk reaches is stored once, below)
     for (size_t i = threadIdx.x; i < (size_t)T * nb * M; i += NW * 64) part[i] = mk<R>(0, 0);
   const R* sq = (const R*)P.sqrt_s + (size_t)b * nk;
   if (COMPACT) {
@@ -455,17 +455,11 @@ __global__ __launch_bounds__(NW * 64) void k_bwd_windows(plan_dev P, swiftcl_inp
       __syncthreads();
     }
     if (cur_band >= 0) flush();
-    // (sub-chunk, band) rows this wavefront never wrote: zeros (the reduction sums every row)
-    if (tt < Tb) {
-      for (int sb = 0; sb < 2; ++sb) {
-        if (pk && sb != hh) continue;
-        for (int bi = 0; bi < nb; ++bi) {
-          if ((flushed >> (sb * SWIFTCL_MAX_BANDS + bi)) & 1u) continue;
-          C2<R>* dst = part + (((size_t)sb * T + tt) * nb + bi) * M;
-#pragma unroll
-          for (int e = 0; e < RL; ++e) dst[lane + SWIFTCL_WAVE * e] = mk<R>(0, 0);
-        }
-      }
+    // the bands whose rows hold something, per sub-chunk
+    if (tt == 0 && lane == 0) {
+      for (int sb = 0; sb < 2; ++sb)
+        if (!pk || sb == hh)
+          P.bwd_bands[2 * slot + sb] = (flushed >> (sb * SWIFTCL_MAX_BANDS)) & ((1u << SWIFTCL_MAX_BANDS) - 1u);
     }
   } else {
     // Software pipeline over the multipoles of this chunk, two barriers per multipole: the adjoint
@@ -499,16 +493,9 @@ __global__ __launch_bounds__(NW * 64) void k_bwd_windows(plan_dev P, swiftcl_inp
     }
     if (NW >= 16) {
       if (cur_band >= 0) flush();
-      // bands this chunk never reached: zero rows (the reduction sums every chunk's row)
-      for (int bi = 0; bi < nb; ++bi) {
-        if ((flushed >> bi) & 1u) continue;
-        for (int t = wave; t < Tb; t += NW) {
-          C2<R>* dst = part + ((size_t)t * nb + bi) * M;
-#pragma unroll
-          for (int e = 0; e < RL; ++e) dst[lane + SWIFTCL_WAVE * e] = mk<R>(0, 0);
-        }
-      }
     }
+    // the bands whose rows hold something (FP64: every row was zeroed first)
+    if (threadIdx.x == 0) P.bwd_bands[slot] = NW >= 16 ? flushed : ~0u;
   }
   if (COMPACT)
     for (int k = threadIdx.x; k < nk; k += NW * 64) dpp[k] = dps[k];  // the loop ended on a barrier
@@ -703,7 +690,7 @@ __global__ __launch_bounds__(256) void k_bwd_gv4(plan_dev P, swiftcl_inputs in, 
 // (a6) Adjoint transforms for one (point, multipole chunk, group of 4 tracers): wave w takes
 // tracer 4 g + w through the chunk's multipoles, dx = 2 s F k^{-1-b} Y from its workspace row,
 // r2c, dc += h conj(X) conj(U_l) in registers, flushed to the (point, chunk, tracer, band)
-// partial row when the band changes; rows of bands the chunk never reaches are zeroed.
+// partial row when the band changes; rows of bands the chunk never reaches are left alone (bwd_bands).
 template <int M, bool TW_LDS>
 __global__ __launch_bounds__(256) void k_bwd_adj(plan_dev P, swiftcl_inputs in, int b0, int nbp, int nlc) {
   constexpr int RL = M / SWIFTCL_WAVE;
@@ -786,11 +773,7 @@ __global__ __launch_bounds__(256) void k_bwd_adj(plan_dev P, swiftcl_inputs in, 
     }
   }
   if (cur_band >= 0) flush();
-  for (int bi = 0; bi < nb; ++bi) {
-    if ((flushed >> bi) & 1u) continue;
-#pragma unroll
-    for (int e = 0; e < RL; ++e) part[(size_t)bi * M + lane + SWIFTCL_WAVE * e] = mk<float>(0.f, 0.f);
-  }
+  if (t == 0 && lane == 0) P.bwd_bands[(size_t)b * nlc + c] = flushed;
 }
 
 // Reduce dc over chunks and take it back through the forward real transform: dg per
@@ -798,6 +781,8 @@ __global__ __launch_bounds__(256) void k_bwd_adj(plan_dev P, swiftcl_inputs in, 
 // wavefronts of a workgroup share the chunk sums of one row, 8 chunks' loads in flight, and the first
 // one transforms (launches of many chunks, few points: 103 chunks of one point took 38 us with one
 // wavefront per row, a load latency per chunk).  Every entry adds its chunks in order, in both.
+constexpr int BWD_LIST = 4096;  // most chunks per point: 2048 of the fused adjoint, 4096 of the workspace adjoint
+
 template <typename R, int M, int WPR>
 __global__ __launch_bounds__(256) void k_bwd_coeffs(plan_dev P, swiftcl_inputs in, int nchunk) {
   __shared__ C2<R> lds[WPR == 1 ? 4 : 1][fft_lds_size(M, sizeof(R))];
@@ -827,28 +812,45 @@ __global__ __launch_bounds__(256) void k_bwd_coeffs(plan_dev P, swiftcl_inputs i
     return;
   }
   const size_t stride = (size_t)T * nb * M;  // chunk stride of the partial rows
+  const unsigned int* bands = P.bwd_bands + (size_t)b * nchunk;  // chunks that reached this band
   const C2<R>* src = (const C2<R>*)P.dchat_part + (((size_t)b * nchunk * T + t) * nb + bi) * M;
   C2<R> v[RL];
   if constexpr (WPR == 1) {
 #pragma unroll
     for (int e = 0; e < RL; ++e) v[e] = mk<R>(0, 0);
     for (int c = 0; c < nchunk; ++c) {
+      if (!((bands[c] >> bi) & 1u)) continue;
 #pragma unroll
       for (int e = 0; e < RL; ++e) v[e] = cadd(v[e], src[c * stride + lane + SWIFTCL_WAVE * e]);
     }
   } else {
+    // the chunks that reached this band, in order
     __shared__ C2<R> sum[M];
+    __shared__ unsigned short list[BWD_LIST];
+    __shared__ int count;
+    if (wave == 0) {
+      int n = 0;
+      for (int c0 = 0; c0 < nchunk; c0 += SWIFTCL_WAVE) {
+        const bool on = c0 + lane < nchunk && ((bands[c0 + lane] >> bi) & 1u);
+        const unsigned long long m = __ballot(on);
+        if (on) list[n + __popcll(m & ((1ull << lane) - 1ull))] = (unsigned short)(c0 + lane);
+        n += __popcll(m);
+      }
+      if (lane == 0) count = n;
+    }
+    __syncthreads();
+    const int nl = count;
     for (int n = threadIdx.x; n < M; n += 256) {
       C2<R> a = mk<R>(0, 0);
       int c = 0;
-      for (; c + 8 <= nchunk; c += 8) {
+      for (; c + 8 <= nl; c += 8) {
         C2<R> x[8];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) x[q] = src[(c + q) * stride + n];
+        for (int q = 0; q < 8; ++q) x[q] = src[list[c + q] * stride + n];
 #pragma unroll
         for (int q = 0; q < 8; ++q) a = cadd(a, x[q]);
       }
-      for (; c < nchunk; ++c) a = cadd(a, src[c * stride + n]);
+      for (; c < nl; ++c) a = cadd(a, src[list[c] * stride + n]);
       sum[n] = a;
     }
     __syncthreads();
@@ -878,7 +880,7 @@ __global__ __launch_bounds__(256) void k_bwd_coeffs(plan_dev P, swiftcl_inputs i
 template <typename R, int M>
 static hipError_t launch_bwd_coeffs(const plan_dev& p, const swiftcl_inputs* in, int nchunk, hipStream_t s) {
   const long rows = (long)in->batch * p.max_tracers * p.n_bands;
-  if (nchunk >= 8 && rows <= 4 * p.persist_blocks)
+  if (nchunk >= 8 && nchunk <= BWD_LIST && rows <= 4 * p.persist_blocks)
     hipLaunchKernelGGL((k_bwd_coeffs<R, M, 4>), dim3((unsigned)rows), dim3(256), 0, s, p, *in, nchunk);
   else
     hipLaunchKernelGGL((k_bwd_coeffs<R, M, 1>), dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, p, *in, nchunk);

@@ -56,24 +56,36 @@ __device__ __forceinline__ v4f mfma_bf16(v8us a, v8us b, v4f c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, a), __builtin_bit_cast(v8bf, b), c, 0, 0, 0);
 }
 
-template <typename R>
-__global__ void k_sqrt_s(plan_dev P, swiftcl_inputs in) {
-  const int b = blockIdx.y;
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= in.batch || j >= P.n_k) return;
+// sqrt(s) of k node j of point b, and kscale * sqrt(s) for every kind and band: the projection scales its
+// windows once
+template <typename R> __device__ __forceinline__ void sqrt_s_node(const plan_dev& P, const swiftcl_inputs& in, int b, int j) {
   const double v = P.kw[j] * in.pk[(size_t)b * P.n_k + j];
   if (!(v >= 0.0) || !isfinite(v)) atomicOr(P.flags, FLAG_NONFINITE);
   const R sq = (R)sqrt(fmax(v, 0.0));
   ((R*)P.sqrt_s)[(size_t)b * P.n_k + j] = sq;
-  // kscale * sqrt(s) for every kind and band: the projection scales its windows once
   for (int kb = 0; kb < SWIFTCL_NKINDS * P.n_bands; ++kb)
     ((R*)P.kss)[((size_t)b * SWIFTCL_NKINDS * P.n_bands + kb) * P.n_k + j] = ((const R*)P.kscale)[(size_t)kb * P.n_k + j] * sq;
 }
 
+template <typename R>
+__global__ void k_sqrt_s(plan_dev P, swiftcl_inputs in) {
+  const int b = blockIdx.y;
+  const int j = blockIdx.x * blockDim.x + threadIdx.x;
+  if (b < in.batch && j < P.n_k) sqrt_s_node<R>(P, in, b, j);
+}
+
 // FFTLog coefficients: one wavefront per (point, tracer, band) row.  SET 0: the kernels; 1: the RSD
-// kernels; 2: the magnification kernels (tilted with the bias b - 2, hence the extra chi_0^2).
+// kernels; 2: the magnification kernels (tilted with the bias b - 2, hence the extra chi_0^2).  The
+// workgroups after the rows (SET 0) form sqrt(s), 256 k nodes each: work of the same size as the rows of a
+// point, in place of a launch of 5 us.
 template <typename R, int M, int SET = 0>
-__global__ __launch_bounds__(256) void k_forward_fft(plan_dev P, swiftcl_inputs in) {
+__global__ __launch_bounds__(256) void k_forward_fft(plan_dev P, swiftcl_inputs in, int nrow) {
+  if (SET == 0 && (int)blockIdx.x >= nrow) {  // (nrow: workgroups of rows)
+    const int nj = (P.n_k + 255) / 256, at = blockIdx.x - nrow;
+    const int j = at % nj * 256 + threadIdx.x;
+    if (j < P.n_k) sqrt_s_node<R>(P, in, at / nj, j);
+    return;
+  }
   __shared__ C2<R> lds[4][fft_lds_size(M, sizeof(R))];
   // FP32: the twiddle table staged in LDS by the block (FP64 reads it through the cache)
   constexpr bool TWS = sizeof(R) == 4;
@@ -454,14 +466,12 @@ __global__ void k_zero_padded(plan_dev P, swiftcl_inputs in, R* __restrict__ Cou
 
 template <typename R, int M>
 static hipError_t launch_fwd_t(const plan_dev& p, const swiftcl_inputs* in, hipStream_t s) {
-  hipLaunchKernelGGL(k_sqrt_s<R>, dim3((p.n_k + 255) / 256, in->batch), dim3(256), 0, s, p, *in);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
   const long rows = (long)in->batch * p.max_tracers * p.n_bands;
-  hipLaunchKernelGGL((k_forward_fft<R, M>), dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, p, *in);
-  if (p.rsd) hipLaunchKernelGGL((k_forward_fft<R, M, 1>), dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, p, *in);
-  if (p.mag && in->mag)
-    hipLaunchKernelGGL((k_forward_fft<R, M, 2>), dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, p, *in);
+  const int nrow = (int)((rows + 3) / 4);
+  hipLaunchKernelGGL((k_forward_fft<R, M>), dim3((unsigned)nrow + (unsigned)((size_t)in->batch * ((p.n_k + 255) / 256))),
+                     dim3(256), 0, s, p, *in, nrow);
+  if (p.rsd) hipLaunchKernelGGL((k_forward_fft<R, M, 1>), dim3(nrow), dim3(256), 0, s, p, *in, nrow);
+  if (p.mag && in->mag) hipLaunchKernelGGL((k_forward_fft<R, M, 2>), dim3(nrow), dim3(256), 0, s, p, *in, nrow);
   return hipGetLastError();
 }
 

@@ -18,6 +18,13 @@ __constant__ static const double c_gl_w[SWIFTCL_NGL] = {
     0.17132449237916975, 0.36076157304813894, 0.46791393457269137,
     0.46791393457269137, 0.36076157304813894, 0.17132449237916975};
 
+// lane t's value of v, t uniform
+__device__ __forceinline__ double readlane_f64(double v, int t) {
+  const long long x = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readlane((int)x, t), hi = __builtin_amdgcn_readlane((int)(x >> 32), t);
+  return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
+}
+
 // value (and derivative) of the natural spline on interval i at z; ih = 1/h per interval
 __device__ __forceinline__ double spline_at(const double* __restrict__ x, const double* __restrict__ ih,
                                             const double* __restrict__ y, const double* __restrict__ Mv, int i,
@@ -149,6 +156,32 @@ __device__ __forceinline__ void lens_interval(double a, double c, int ig, int iv
   *s1 = r1;
 }
 
+// One step of a wavefront scan: the value of the lane that the DPP control names, `old` where it names none.
+template <int CTRL, int ROWS> __device__ __forceinline__ double dpp_move(double old, double v) {
+  const long long o = __double_as_longlong(old), x = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp((int)o, (int)x, CTRL, ROWS, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp((int)(o >> 32), (int)(x >> 32), CTRL, ROWS, 0xf, false);
+  return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
+}
+
+// Inclusive scan over the lanes of the affine maps y -> A y + B_r (NR maps of one slope): on return lane i
+// holds the composition of the maps of lanes 0..i, lane 0's applied first.  Row shifts by 1, 2, 4, 8 within
+// 16 lanes, then the last lane of the row before (0x142) and of the half before (0x143).
+template <int NR, int CTRL, int ROWS> __device__ __forceinline__ void affine_step(double& A, double (&B)[NR]) {
+  const double Ap = dpp_move<CTRL, ROWS>(1.0, A);
+#pragma unroll
+  for (int r = 0; r < NR; ++r) B[r] = A * dpp_move<CTRL, ROWS>(0.0, B[r]) + B[r];
+  A *= Ap;
+}
+template <int NR> __device__ __forceinline__ void affine_scan(double& A, double (&B)[NR]) {
+  affine_step<NR, 0x111, 0xf>(A, B);
+  affine_step<NR, 0x112, 0xf>(A, B);
+  affine_step<NR, 0x114, 0xf>(A, B);
+  affine_step<NR, 0x118, 0xf>(A, B);
+  affine_step<NR, 0x142, 0xa>(A, B);
+  affine_step<NR, 0x143, 0xc>(A, B);
+}
+
 // Wavefront-parallel solve of the natural-spline tridiagonal system A z = rhs on the interior
 // rows 1..n-2 (A is symmetric; Thomas factors a, 1/pivot, c' of the grid in lu).  x holds rhs on
 // entry and z on exit (LDS); x[0] and x[n-1] are set to 0.  The two Thomas recurrences are
@@ -162,6 +195,57 @@ __device__ inline void wave_tridiag_solve(double* __restrict__ x, const double* 
   const int C = (rows + SWIFTCL_WAVE - 1) / SWIFTCL_WAVE;
   const int lo = 1 + lane * C;
   const int hi = min(1 + (lane + 1) * C, n - 1);
+  // a lane's rows and factors in registers, up to four rows per lane (every grid of up to
+  // 258 samples): the loads are issued together, not one latency per row
+  constexpr int CR = 4;
+  if (C <= CR) {
+    double av[CR], iv[CR], cv[CR], xv[CR];
+#pragma unroll
+    for (int k = 0; k < CR; ++k) {
+      const int i = min(lo + k, n - 1);
+      const bool on = lo + k < hi;
+      av[k] = on ? a[i] : 0.0;
+      iv[k] = on ? inv[i] : 0.0;
+      cv[k] = on ? cp[i] : 0.0;
+      xv[k] = on ? x[i] : 0.0;
+    }
+    // (rows past the end map everything to 0; they only feed rows past the end)
+    double A = 1.0, B[1] = {0.0};
+#pragma unroll
+    for (int k = 0; k < CR; ++k) {
+      if (lo + k < hi) {
+        const double al = -av[k] * iv[k];
+        A *= al;
+        B[0] = al * B[0] + xv[k] * iv[k];
+      }
+    }
+    affine_scan<1>(A, B);
+    double prev = __shfl_up(B[0], 1);
+    if (lane == 0) prev = 0.0;
+#pragma unroll
+    for (int k = 0; k < CR; ++k) xv[k] = prev = (xv[k] - av[k] * prev) * iv[k];
+    A = 1.0;
+    double D = 0.0;
+#pragma unroll
+    for (int k = CR - 1; k >= 0; --k) {
+      if (lo + k < hi) {
+        A *= -cv[k];
+        D = xv[k] - cv[k] * D;
+      }
+    }
+    for (int off = 1; off < SWIFTCL_WAVE; off <<= 1) {
+      const double Ap = __shfl_down(A, off), Dp = __shfl_down(D, off);
+      if (lane + off < SWIFTCL_WAVE) { D = A * Dp + D; A = A * Ap; }
+    }
+    double next = __shfl_down(D, 1);
+    if (lane == SWIFTCL_WAVE - 1) next = 0.0;
+#pragma unroll
+    for (int k = CR - 1; k >= 0; --k) {
+      if (lo + k < hi) x[lo + k] = next = xv[k] - cv[k] * next;
+    }
+    if (lane == 0) { x[0] = 0.0; x[n - 1] = 0.0; }
+    return;
+  }
   double A = 1.0, B = 0.0;
   for (int i = lo; i < hi; ++i) {
     const double al = -a[i] * inv[i], be = x[i] * inv[i];
@@ -207,32 +291,6 @@ __device__ inline void wave_spline(const double* __restrict__ y, const double* _
   wave_sync();
   wave_tridiag_solve(Mo, lu, n, lane);
   wave_sync();
-}
-
-// One step of a wavefront scan: the value of the lane that the DPP control names, `old` where it names none.
-template <int CTRL, int ROWS> __device__ __forceinline__ double dpp_move(double old, double v) {
-  const long long o = __double_as_longlong(old), x = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_update_dpp((int)o, (int)x, CTRL, ROWS, 0xf, false);
-  const int hi = __builtin_amdgcn_update_dpp((int)(o >> 32), (int)(x >> 32), CTRL, ROWS, 0xf, false);
-  return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
-}
-
-// Inclusive scan over the lanes of the affine maps y -> A y + B_r (NR maps of one slope): on return lane i
-// holds the composition of the maps of lanes 0..i, lane 0's applied first.  Row shifts by 1, 2, 4, 8 within
-// 16 lanes, then the last lane of the row before (0x142) and of the half before (0x143).
-template <int NR, int CTRL, int ROWS> __device__ __forceinline__ void affine_step(double& A, double (&B)[NR]) {
-  const double Ap = dpp_move<CTRL, ROWS>(1.0, A);
-#pragma unroll
-  for (int r = 0; r < NR; ++r) B[r] = A * dpp_move<CTRL, ROWS>(0.0, B[r]) + B[r];
-  A *= Ap;
-}
-template <int NR> __device__ __forceinline__ void affine_scan(double& A, double (&B)[NR]) {
-  affine_step<NR, 0x111, 0xf>(A, B);
-  affine_step<NR, 0x112, 0xf>(A, B);
-  affine_step<NR, 0x114, 0xf>(A, B);
-  affine_step<NR, 0x118, 0xf>(A, B);
-  affine_step<NR, 0x142, 0xa>(A, B);
-  affine_step<NR, 0x143, 0xc>(A, B);
 }
 
 // The solve of wave_tridiag_solve by a whole workgroup for NR right-hand sides x[r] of one grid (LDS, rhs

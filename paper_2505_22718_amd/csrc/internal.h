@@ -77,6 +77,7 @@ struct plan_dev {
   int* flags;       // [1]
   // backward workspace
   void* dchat_part; // [bwd_slots][T][n_bands][M] complex real: dc partials per (point, chunk)
+  unsigned int* bwd_bands;  // [bwd_slots] bit bi: the slot's rows of band bi are written (others hold nothing)
   void* dpk_part;   // [bwd_slots][n_k] real: sum_t W Y partials per (point, chunk)
   void* dg;         // [B][T][n_bands][N] real
   int bwd_slots;    // capacity of (point, chunk) slots

@@ -329,7 +329,7 @@ static void free_plan(swiftcl_plan_s* p) {
   void* ptrs[] = {p->d.U, p->d.kscale, p->d.tw, p->d.fell, p->d.ell_band, p->d.kw, p->d.ell_v, p->d.lnk, p->d.lu_k,
                   p->d.lnp, p->d.lim_acc, p->d.ebm, p->d.z_geom, p->d.z_nz, p->d.lu_geom,
                   p->d.lu_nz, p->d.z_union, p->d.union_iv, p->d.union_g, p->d.pt, p->d.m_chi, p->d.m_D, p->d.m_ia, p->d.m_n, p->d.lens_q, p->d.phase, p->d.node_f, p->d.node_i, p->d.ddD_part, p->d.g,
-                  p->d.chat, p->d.sqrt_s, p->d.kss, p->d.flags, p->d.dchat_part, p->d.dpk_part, p->d.dg, p->d.sched, p->d.bwd_order, p->d.vbuf,
+                  p->d.chat, p->d.sqrt_s, p->d.kss, p->d.flags, p->d.dchat_part, p->d.bwd_bands, p->d.dpk_part, p->d.dg, p->d.sched, p->d.bwd_order, p->d.vbuf,
                   p->d.kg_ones, p->d.kg_ia, p->d.kg_w, p->d.kg_ip, p->d.kg_uh, p->d.kg_c, p->d.kg_m, p->d.kg_perm,
                   p->d.kg_tile, p->d.kc_w, p->d.kc_ip, p->d.kc_u, p->d.kc_tw, p->d.kc_dn, p->d.kc_dm, p->d.kc_dt,
                   p->d.kc_f, p->d.kc_k, p->d.UR, p->d.g_r, p->d.chat_r, p->d.Umu, p->d.g_mu, p->d.chat_mu};
@@ -663,6 +663,7 @@ extern "C" swiftcl_status swiftcl_plan(const swiftcl_plan_desc* d, void* stream,
     p->d.bwd_slots = std::max(p->d.bwd_slots, (int)(nlc * B));
   }
   ALLOC(dchat_part, char, (size_t)p->d.bwd_slots * T * nb * M * 2 * rs);
+  ALLOC(bwd_bands, unsigned int, p->d.bwd_slots);
   ALLOC(dpk_part, char, (size_t)p->d.bwd_slots * nk * rs);
   ALLOC(dg, char, (size_t)B * T * nb * N * rs);
 #undef ALLOC

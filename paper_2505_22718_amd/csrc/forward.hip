@@ -511,16 +511,201 @@ constexpr bool unfused_tw(int M) { return M <= 1024; }
 bool unfused_tw_lds(int M) { return unfused_tw(M); }
 
 // ---------------------------------------------------------------------------------------------
-// Unfused projection for more than 16 tracers or windows too large for LDS (FP32 / split):
-// k_windows_v writes V = sqrt(s) W of up to 32 tracer slots per (point, multipole) to the
-// workspace, k_contract forms the 32 x 32 Gram matrix from three 16 x 16 MFMA tile pairs
-// (0,0), (0,1), (1,1).  Points are processed in chunks of P.vchunk.
-// ---------------------------------------------------------------------------------------------
+// Projection of plans that k_windows_cl does not hold (17..32 tracers, n_chi = 2048, RSD and
+// magnification; FP32 / split): one workgroup of 16 wavefronts per (point, multipole slot), wavefront w
+// transforms the tracers w and (NT = 2) w + 16 and keeps sqrt(s) W of both in registers, 2 NT RL floats
+// per lane.  The rows meet in LDS a slab of k at a time, double-buffered in the space of the transforms'
+// scratch (one barrier per slab), and the Gram tiles (0,0), (0,1), (1,1) accumulate over the slabs on MFMA,
+// so that no window reaches HBM.  Through a workspace (rows written, then read by a contraction) 64 points
+// of 30 tracers, 200 multipoles and n_k = 2048 moved 6.6 GB and took 2.5 ms; this takes 1.30 ms, bound by
+// the FP32 issue of the transforms.
 // EXTRA bit 1: the plan carries RSD, bit 2: magnification (used when the inputs give C_g).
-// w_only = 1 (FP32, the adjoint's recompute): the rows hold W = F(l) kscale c2r(...) itself, not
-// sqrt(s) W.
-template <int M, int NW, bool TW_LDS, bool SPLIT, int EXTRA>
-__global__ __launch_bounds__(NW * 64) void k_windows_v(plan_dev P, swiftcl_inputs in, int b0, int nbp, int w_only) {
+// ---------------------------------------------------------------------------------------------
+template <int M, int NT> struct wp_shape {
+  static constexpr int RL = M / SWIFTCL_WAVE;
+  static constexpr int SE = NT == 2 ? (RL >= 4 ? RL / 4 : 1) : RL / 2;  // registers pairs per slab
+  static constexpr int NS = RL / SE;                                    // slabs
+  static constexpr int SW = 2 * SWIFTCL_WAVE * SE;                      // k nodes per slab
+  static constexpr int SP = SW + 4;                                     // row stride: 16-byte reads on distinct banks
+  static constexpr int TILES = NT == 2 ? 3 : 1;
+  static constexpr size_t bytes(bool tw) {
+    size_t n = (size_t)16 * fft_lds_size(M, 4) * 8;
+    if ((size_t)2 * 16 * NT * SP * 4 > n) n = (size_t)2 * 16 * NT * SP * 4;
+    if ((size_t)16 * TILES * 1024 > n) n = (size_t)16 * TILES * 1024;
+    return n + (tw ? (size_t)2 * M * 8 : 0);
+  }
+};
+
+// d_n conjugated of one window: c_n U_l(n) and the RSD and magnification terms of a clustering tracer,
+// which share its prefactor and k scale
+template <int M, int EXTRA>
+__device__ __forceinline__ void window_coeffs(const plan_dev& P, const swiftcl_inputs& in, int b, int t, int kind,
+                                              int ei, int band, int lane, float2 (&v)[M / SWIFTCL_WAVE]) {
+  typedef float R;
+  constexpr int RL = M / SWIFTCL_WAVE;
+  const size_t row = (((size_t)b * P.max_tracers + t) * P.n_bands + band) * M;
+  const C2<R>* ch = (const C2<R>*)P.chat + row;
+  const C2<R>* Ur = (const C2<R>*)P.U + ((size_t)kind * P.n_ell + ei) * M;
+#pragma unroll
+  for (int e = 0; e < RL; ++e) {
+    const int n = lane + SWIFTCL_WAVE * e;
+    v[e] = cconj(cmul(ch[n], Ur[n]));
+  }
+  if ((EXTRA & 1) && kind == SWIFTCL_CLUSTERING) {
+    const C2<R>* chr = (const C2<R>*)P.chat_r + row;
+    const C2<R>* URr = (const C2<R>*)P.UR + (size_t)ei * M;
+#pragma unroll
+    for (int e = 0; e < RL; ++e) {
+      const int n = lane + SWIFTCL_WAVE * e;
+      v[e] = cadd(v[e], cconj(cmul(chr[n], URr[n])));
+    }
+  }
+  if ((EXTRA & 2) && in.mag && kind == SWIFTCL_CLUSTERING) {
+    // l(l+1) U at the bias b - 2
+    const C2<R>* chm = (const C2<R>*)P.chat_mu + row;
+    const C2<R>* Umr = (const C2<R>*)P.Umu + (size_t)ei * M;
+#pragma unroll
+    for (int e = 0; e < RL; ++e) {
+      const int n = lane + SWIFTCL_WAVE * e;
+      v[e] = cadd(v[e], cconj(cmul(chm[n], Umr[n])));
+    }
+  }
+}
+
+template <int M, int NT, bool TW_LDS, bool SPLIT, int EXTRA>
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(M <= 512 ? 8 : 4))) void k_windows_p(
+    plan_dev P, swiftcl_inputs in, float* __restrict__ Cout) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  using S = wp_shape<M, NT>;
+  typedef float R;
+  constexpr int RL = S::RL, N = 2 * M, FL = fft_lds_size(M, sizeof(R));
+  C2<R>* stw_l = (C2<R>*)smem;                                    // [N] (TW_LDS)
+  C2<R>* fbuf = stw_l + (TW_LDS ? N : 0);                         // [16][FL] transform scratch, then
+  float* slab = (float*)fbuf;                                     // [2][16 NT][SP], then [16][TILES][256]
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / SWIFTCL_WAVE), lane = threadIdx.x % SWIFTCL_WAVE;
+  const int T = P.max_tracers, Lm = P.max_ell, nk = P.n_k, nb = P.n_bands;
+  int b, li;
+  xcd_item(blockIdx.x, in.batch, Lm, &b, &li);
+  if (b >= in.batch) return;
+  const int Tb = clampi(in.n_tracers[b], 0, T);
+  const int npair = T * (T + 1) / 2;
+  float* c = Cout + ((size_t)b * Lm + li) * npair;
+  if (li >= clampi(in.n_ell[b], 0, Lm)) {
+    for (int i = threadIdx.x; i < npair; i += 1024) c[i] = 0.f;
+    return;
+  }
+  int ei = in.ell_idx[(size_t)b * Lm + li];
+  if (ei < 0 || ei >= P.n_ell) {
+    if (threadIdx.x == 0) atomicOr(P.flags, FLAG_BAD_INDEX);
+    ei = 0;
+  }
+  const int band = P.ell_band[ei];
+  const C2<R>* stw = TW_LDS ? stw_l : (const C2<R>*)P.tw;
+  if constexpr (TW_LDS) {
+    for (int i = threadIdx.x; i < N; i += 1024) stw_l[i] = ((const C2<R>*)P.tw)[i];
+    __syncthreads();
+  }
+  C2<R> x[NT][RL];
+#pragma unroll
+  for (int i = 0; i < NT; ++i) {
+    const int t = wave + 16 * i;
+#pragma unroll
+    for (int e = 0; e < RL; ++e) x[i][e] = mk<R>(0.f, 0.f);
+    if (t >= Tb) continue;
+    const int kind = tracer_kind(in, T, b, t);
+    window_coeffs<M, EXTRA>(P, in, b, t, kind, ei, band, lane, x[i]);
+    int ln = lane;  // opaque copy: keeps the FFT's per-lane LDS addresses out of the tracer loop
+    asm volatile("" : "+v"(ln));
+    ln &= SWIFTCL_WAVE - 1;
+    wave_sync();
+    wave_c2r<R, M>(x[i], fbuf + (size_t)wave * FL, stw, ln);
+    const R* kq = (const R*)P.kss + (((size_t)b * SWIFTCL_NKINDS + kind) * nb + band) * nk;  // kscale sqrt(s)
+#pragma unroll
+    for (int e = 0; e < RL; ++e) {
+      const int k0 = 2 * (ln + SWIFTCL_WAVE * e);
+      const C2<R> kk = *(const C2<R>*)(kq + min(k0, nk - 2));  // (nk is even)
+      x[i][e] = k0 < nk ? mk<R>(kk.x * x[i][e].x, kk.y * x[i][e].y) : mk<R>(0.f, 0.f);
+    }
+  }
+  __syncthreads();  // the scratch is free
+  v4f acc[S::TILES];
+#pragma unroll
+  for (int i = 0; i < S::TILES; ++i) acc[i] = (v4f){0.f, 0.f, 0.f, 0.f};
+  const int r = lane & 15, q = lane >> 4;
+#pragma unroll
+  for (int s = 0; s < S::NS; ++s) {
+    float* V = slab + (size_t)(s & 1) * 16 * NT * S::SP;
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+      for (int e = 0; e < S::SE; ++e)
+        *(C2<R>*)(V + (wave + 16 * i) * S::SP + 2 * (lane + SWIFTCL_WAVE * e)) = x[i][s * S::SE + e];
+    __syncthreads();  // (the other buffer was last read before this barrier)
+    if constexpr (SPLIT) {
+      // 16x16x32 bf16: lane (r, q) feeds 8 consecutive k of row r, split into hi + lo
+      for (int st = wave; st < S::SW / 32; st += 16) {
+        v8us h[NT], l[NT];
+#pragma unroll
+        for (int i = 0; i < NT; ++i) {
+          const float* a = V + (16 * i + r) * S::SP + 32 * st + 8 * q;
+          const v4f a0 = *(const v4f*)a, a1 = *(const v4f*)(a + 4);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            unsigned short hi, lo;
+            split_bf16(e < 4 ? a0[e & 3] : a1[e & 3], &hi, &lo);
+            h[i][e] = hi;
+            l[i][e] = lo;
+          }
+        }
+#pragma unroll
+        for (int g = 0; g < S::TILES; ++g) {
+          const int i = g == 2 ? 1 : 0, j = g == 0 ? 0 : NT - 1;
+          acc[g] = mfma_bf16(h[i], h[j], acc[g]);
+          acc[g] = mfma_bf16(h[i], l[j], acc[g]);
+          acc[g] = mfma_bf16(l[i], h[j], acc[g]);
+        }
+      }
+    } else {
+      // 16x16x4 f32, the k order free (V is both operands): lane (r, q) feeds k = 16 st + 4 q + m at step m
+      for (int st = wave; st < S::SW / 16; st += 16) {
+        v4f a[NT];
+#pragma unroll
+        for (int i = 0; i < NT; ++i) a[i] = *(const v4f*)(V + (16 * i + r) * S::SP + 16 * st + 4 * q);
+#pragma unroll
+        for (int m = 0; m < 4; ++m)
+#pragma unroll
+          for (int g = 0; g < S::TILES; ++g)
+            acc[g] = mfma_acc<float>::step(a[g == 2 ? 1 : 0][m], a[g == 0 ? 0 : NT - 1][m], acc[g]);
+      }
+    }
+  }
+  __syncthreads();  // every slab is read
+  // rows 4q..4q+3 of column r of each tile: red[wave][tile][16 r + 4 q + 0..3]
+  float* red = slab;
+#pragma unroll
+  for (int g = 0; g < S::TILES; ++g) *(v4f*)(red + (wave * S::TILES + g) * 256 + 16 * r + 4 * q) = acc[g];
+  __syncthreads();
+  for (int idx = threadIdx.x; idx < npair; idx += 1024) {
+    int i = 0, rem = idx;
+    while (rem >= T - i) { rem -= T - i; ++i; }
+    const int j = i + rem;
+    float val = 0.f;
+    if (i < Tb && j < Tb) {
+      const int g = (i < 16) ? (j < 16 ? 0 : 1) : 2;
+      const int e = (j % 16) * 16 + (i % 16);  // row i, column j of the tile
+#pragma unroll
+      for (int w = 0; w < 16; ++w) val += red[(w * S::TILES + g) * 256 + e];
+    }
+    c[idx] = val;
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
+// The windows W = F(l) kscale c2r(...) of up to 32 tracer slots per (point, multipole) into the workspace
+// (FP32), for the adjoint; points in chunks of P.vchunk.
+// ---------------------------------------------------------------------------------------------
+template <int M, int NW, bool TW_LDS, int EXTRA>
+__global__ __launch_bounds__(NW * 64) void k_windows_v(plan_dev P, swiftcl_inputs in, int b0, int nbp) {
   extern __shared__ __align__(16) unsigned char smem[];
   typedef float R;
   constexpr int RL = M / SWIFTCL_WAVE;
@@ -538,14 +723,9 @@ __global__ __launch_bounds__(NW * 64) void k_windows_v(plan_dev P, swiftcl_input
   const int Tb = clampi(in.n_tracers[b], 0, T);
   const int Lb = clampi(in.n_ell[b], 0, Lm);
   const size_t row0 = ((size_t)bl * Lm + li) * 32;
-  const size_t lo_off = (size_t)P.vchunk * Lm * 32 * nk;  // split: lo parts after all hi parts
   float* vf = (float*)P.vbuf;
-  unsigned short* vh = (unsigned short*)P.vbuf;
   if (li >= Lb) {
-    for (size_t i = threadIdx.x; i < (size_t)32 * nk; i += NW * 64) {
-      if (SPLIT) { vh[row0 * nk + i] = 0; vh[lo_off + row0 * nk + i] = 0; }
-      else vf[row0 * nk + i] = 0.f;
-    }
+    for (size_t i = threadIdx.x; i < (size_t)32 * nk; i += NW * 64) vf[row0 * nk + i] = 0.f;
     return;
   }
   int ei = in.ell_idx[(size_t)b * Lm + li];
@@ -564,70 +744,29 @@ __global__ __launch_bounds__(NW * 64) void k_windows_v(plan_dev P, swiftcl_input
   for (int t = wave; t < 32; t += NW) {
     const size_t rb = (row0 + t) * nk;
     if (t >= Tb) {
-      for (int j = lane; j < nk; j += SWIFTCL_WAVE) {
-        if (SPLIT) { vh[rb + j] = 0; vh[lo_off + rb + j] = 0; }
-        else vf[rb + j] = 0.f;
-      }
+      for (int j = lane; j < nk; j += SWIFTCL_WAVE) vf[rb + j] = 0.f;
       continue;
     }
     const int kind = tracer_kind(in, T, b, t);
-    const C2<R>* ch = (const C2<R>*)P.chat + (((size_t)b * T + t) * nb + band) * M;
-    const C2<R>* Ur = (const C2<R>*)P.U + ((size_t)kind * P.n_ell + ei) * M;
     C2<R> v[RL];
     wave_sync();
-#pragma unroll
-    for (int e = 0; e < RL; ++e) {
-      const int n = lane + SWIFTCL_WAVE * e;
-      v[e] = cconj(cmul(ch[n], Ur[n]));
-    }
-    if ((EXTRA & 1) && kind == SWIFTCL_CLUSTERING) {
-      // the RSD window of a clustering tracer shares its prefactor and k scale: add its term
-      const C2<R>* chr = (const C2<R>*)P.chat_r + (((size_t)b * T + t) * nb + band) * M;
-      const C2<R>* URr = (const C2<R>*)P.UR + (size_t)ei * M;
-#pragma unroll
-      for (int e = 0; e < RL; ++e) {
-        const int n = lane + SWIFTCL_WAVE * e;
-        v[e] = cadd(v[e], cconj(cmul(chr[n], URr[n])));
-      }
-    }
-    if ((EXTRA & 2) && in.mag && kind == SWIFTCL_CLUSTERING) {
-      // magnification: l(l+1) U at the bias b - 2 shares the density window's k scale
-      const C2<R>* chm = (const C2<R>*)P.chat_mu + (((size_t)b * T + t) * nb + band) * M;
-      const C2<R>* Umr = (const C2<R>*)P.Umu + (size_t)ei * M;
-#pragma unroll
-      for (int e = 0; e < RL; ++e) {
-        const int n = lane + SWIFTCL_WAVE * e;
-        v[e] = cadd(v[e], cconj(cmul(chm[n], Umr[n])));
-      }
-    }
+    window_coeffs<M, EXTRA>(P, in, b, t, kind, ei, band, lane, v);
     int ln = lane;  // opaque copy: keeps the FFT's per-lane LDS addresses out of the tracer loop
     asm volatile("" : "+v"(ln));
     ln &= SWIFTCL_WAVE - 1;
     wave_c2r<R, M>(v, mine, stw, ln);
-    const R* kq = w_only ? (const R*)P.kscale + ((size_t)kind * nb + band) * nk
-                         : (const R*)P.kss + (((size_t)b * SWIFTCL_NKINDS + kind) * nb + band) * nk;  // kscale sqrt(s)
+    const R* kq = (const R*)P.kscale + ((size_t)kind * nb + band) * nk;
     constexpr int KG = RL < 4 ? RL : 4;  // loads issued in groups (index clamped into the row, nk even)
 #pragma unroll
     for (int e0 = 0; e0 < RL; e0 += KG) {
-    C2<R> kk[KG];
+      C2<R> kk[KG];
 #pragma unroll
-    for (int e = 0; e < KG; ++e) kk[e] = *(const C2<R>*)(kq + min(2 * (ln + SWIFTCL_WAVE * (e0 + e)), nk - 2));
+      for (int e = 0; e < KG; ++e) kk[e] = *(const C2<R>*)(kq + min(2 * (ln + SWIFTCL_WAVE * (e0 + e)), nk - 2));
 #pragma unroll
-    for (int e = 0; e < KG; ++e) {
-      const int k0 = 2 * (ln + SWIFTCL_WAVE * (e0 + e));
-      if (k0 < nk) {
-        const float x0 = kk[e].x * v[e0 + e].x, x1 = kk[e].y * v[e0 + e].y;
-        if (SPLIT) {
-          unsigned short h0, l0, h1, l1;
-          split_bf16(x0, &h0, &l0);
-          split_bf16(x1, &h1, &l1);
-          *(unsigned int*)(vh + rb + k0) = (unsigned int)h0 | ((unsigned int)h1 << 16);
-          *(unsigned int*)(vh + lo_off + rb + k0) = (unsigned int)l0 | ((unsigned int)l1 << 16);
-        } else {
-          *(C2<R>*)(vf + rb + k0) = mk<R>(x0, x1);
-        }
+      for (int e = 0; e < KG; ++e) {
+        const int k0 = 2 * (ln + SWIFTCL_WAVE * (e0 + e));
+        if (k0 < nk) *(C2<R>*)(vf + rb + k0) = mk<R>(kk[e].x * v[e0 + e].x, kk[e].y * v[e0 + e].y);
       }
-    }
     }
   }
 }
@@ -773,29 +912,25 @@ hipError_t launch_sqrt_s(const plan_dev& p, const swiftcl_inputs* in, hipStream_
 
 template <int M>
 static hipError_t launch_unfused(const plan_dev& p, const swiftcl_inputs* in, void* C, hipStream_t s) {
-  constexpr int NW = 16;
   constexpr bool TW = unfused_tw(M);
   const bool split = p.precision == SWIFTCL_SPLIT_BF16;
-  const size_t lds = windows_cl_lds(M, NW, TW, false, sizeof(float), p.n_k);
-  for (int b0 = 0; b0 < in->batch; b0 += p.vchunk) {
-    const int nbp = in->batch - b0 < p.vchunk ? in->batch - b0 : p.vchunk;
-    const dim3 g1(xcd_blocks(nbp, p.max_ell));
-#define SWIFTCL_WV(SP, EX) hipLaunchKernelGGL((k_windows_v<M, NW, TW, SP, EX>), g1, dim3(NW * 64), lds, s, p, *in, b0, nbp, 0)
-    switch ((p.rsd ? 1 : 0) | (p.mag ? 2 : 0)) {
-      case 0: if (split) SWIFTCL_WV(true, 0); else SWIFTCL_WV(false, 0); break;
-      case 1: if (split) SWIFTCL_WV(true, 1); else SWIFTCL_WV(false, 1); break;
-      case 2: if (split) SWIFTCL_WV(true, 2); else SWIFTCL_WV(false, 2); break;
-      default: if (split) SWIFTCL_WV(true, 3); else SWIFTCL_WV(false, 3); break;
-    }
-#undef SWIFTCL_WV
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const dim3 g2((unsigned)((size_t)nbp * p.max_ell));
-    if (split) hipLaunchKernelGGL(k_contract<true>, g2, dim3(256), 0, s, p, *in, (float*)C, b0, nbp);
-    else hipLaunchKernelGGL(k_contract<false>, g2, dim3(256), 0, s, p, *in, (float*)C, b0, nbp);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+  const dim3 grid(xcd_blocks(in->batch, p.max_ell));
+#define SWIFTCL_WP(NT, SP, EX) \
+  hipLaunchKernelGGL((k_windows_p<M, NT, TW, SP, EX>), grid, dim3(1024), (wp_shape<M, NT>::bytes(TW)), s, p, *in, (float*)C)
+#define SWIFTCL_WP2(SP, EX)                \
+  do {                                     \
+    if (p.max_tracers > 16) SWIFTCL_WP(2, SP, EX); \
+    else SWIFTCL_WP(1, SP, EX);            \
+  } while (0)
+  switch ((p.rsd ? 1 : 0) | (p.mag ? 2 : 0)) {
+    case 0: if (split) SWIFTCL_WP2(true, 0); else SWIFTCL_WP2(false, 0); break;
+    case 1: if (split) SWIFTCL_WP2(true, 1); else SWIFTCL_WP2(false, 1); break;
+    case 2: if (split) SWIFTCL_WP2(true, 2); else SWIFTCL_WP2(false, 2); break;
+    default: if (split) SWIFTCL_WP2(true, 3); else SWIFTCL_WP2(false, 3); break;
   }
-  return hipSuccess;
+#undef SWIFTCL_WP2
+#undef SWIFTCL_WP
+  return hipGetLastError();
 }
 
 template <int M>
@@ -806,10 +941,10 @@ static hipError_t launch_ww_t(const plan_dev& p, const swiftcl_inputs* in, int b
   const dim3 g1(xcd_blocks(nbp, p.max_ell));
   // the recomputed W carries the RSD and magnification terms of plans built with them
   switch ((p.rsd ? 1 : 0) | (p.mag ? 2 : 0)) {
-    case 0: hipLaunchKernelGGL((k_windows_v<M, NW, TW, false, 0>), g1, dim3(NW * 64), lds, s, p, *in, b0, nbp, 1); break;
-    case 1: hipLaunchKernelGGL((k_windows_v<M, NW, TW, false, 1>), g1, dim3(NW * 64), lds, s, p, *in, b0, nbp, 1); break;
-    case 2: hipLaunchKernelGGL((k_windows_v<M, NW, TW, false, 2>), g1, dim3(NW * 64), lds, s, p, *in, b0, nbp, 1); break;
-    default: hipLaunchKernelGGL((k_windows_v<M, NW, TW, false, 3>), g1, dim3(NW * 64), lds, s, p, *in, b0, nbp, 1); break;
+    case 0: hipLaunchKernelGGL((k_windows_v<M, NW, TW, 0>), g1, dim3(NW * 64), lds, s, p, *in, b0, nbp); break;
+    case 1: hipLaunchKernelGGL((k_windows_v<M, NW, TW, 1>), g1, dim3(NW * 64), lds, s, p, *in, b0, nbp); break;
+    case 2: hipLaunchKernelGGL((k_windows_v<M, NW, TW, 2>), g1, dim3(NW * 64), lds, s, p, *in, b0, nbp); break;
+    default: hipLaunchKernelGGL((k_windows_v<M, NW, TW, 3>), g1, dim3(NW * 64), lds, s, p, *in, b0, nbp); break;
   }
   return hipGetLastError();
 }

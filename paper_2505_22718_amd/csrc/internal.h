@@ -92,12 +92,13 @@ struct plan_dev {
                       // tracers (0 or 1; with bwd_chunk_mul <= 4)
   int* sched;         // sched_ints(sched_stride): per-XCD work lists of the persistent launch
   int sched_stride;
-  // projection path: fused (windows in LDS, <= 16 tracers) or through the workspace below
+  // projection path: fused (windows in LDS, <= 16 tracers) or k_windows_p; the workspace below serves the
+  // adjoint of the latter and scale-dependent growth
   int fused;
   int adjoint;        // swiftcl_cl_backward: 0 not built, 1 fused (windows in LDS), 2 through the workspace
   int bwd_nlc;        // multipole chunks per point of the workspace adjoint
-  int vchunk;         // points per chunk of the unfused path
-  void* vbuf;         // [vchunk][max_ell][32][n_k] FP32, or bf16 hi then lo (unfused and kgrowth paths)
+  int vchunk;         // points per chunk of the workspace
+  void* vbuf;         // [vchunk][max_ell][32][n_k] FP32, or bf16 hi then lo (workspace adjoint and kgrowth paths)
   // scale-dependent growth (swiftcl_cl_kgrowth); points run in chunks of vchunk
   int n_interp;       // k nodes (0 = not built)
   // redshift-space distortions (eq. RSD) of the clustering tracers: a second coefficient set per

@@ -577,8 +577,7 @@ extern "C" swiftcl_status swiftcl_plan(const swiftcl_plan_desc* d, void* stream,
   }
   p->d.n_interp = d->n_interp;
   if (!p->d.fused || p->d.n_interp > 0 || p->d.adjoint == 2) {
-    // workspace of the unfused projection (V of up to 32 tracer slots) and of scale-dependent
-    // growth (node coefficients and their spline moments), a chunk of points at a time
+    // workspace of the adjoint (W of up to 32 tracer slots) and of scale-dependent growth (node coefficients and their spline moments), a chunk of points at a time
     const size_t per_point = (size_t)p->d.max_ell * 32 * nk * 4;
     size_t chunk = ((size_t)512 << 20) / per_point;
     if (p->d.n_interp > 0) {

@@ -14,6 +14,7 @@
 #include "common.h"
 #include "geometry.h"
 #include "internal.h"
+#include "windows.h"
 
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef double v4d __attribute__((ext_vector_type(4)));
@@ -692,7 +693,7 @@ __global__ __launch_bounds__(256) void k_bwd_gv4(plan_dev P, swiftcl_inputs in, 
 // r2c, dc += h conj(X) conj(U_l) in registers, flushed to the (point, chunk, tracer, band)
 // partial row when the band changes; rows of bands the chunk never reaches are left alone (bwd_bands).
 template <int M, bool TW_LDS>
-__global__ __launch_bounds__(256) void k_bwd_adj(plan_dev P, swiftcl_inputs in, int b0, int nbp, int nlc) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_bwd_adj(plan_dev P, swiftcl_inputs in, int b0, int nbp, int nlc) {
   constexpr int RL = M / SWIFTCL_WAVE;
   constexpr int N = 2 * M;
   __shared__ C2<float> lds[4][fft_lds_size(M, sizeof(float))];
@@ -774,6 +775,222 @@ __global__ __launch_bounds__(256) void k_bwd_adj(plan_dev P, swiftcl_inputs in, 
   }
   if (cur_band >= 0) flush();
   if (t == 0 && lane == 0) P.bwd_bands[(size_t)b * nlc + c] = flushed;
+}
+
+// The workspace adjoint of plans of <= 16 tracers and n_chi <= 1024 (RSD and magnification plans) without the
+// workspace: one workgroup of 16 wavefronts per (point, multipole chunk), one tracer per wavefront, with the
+// LDS rows and the pipeline of k_bwd_windows but the sums of k_bwd_gv4 (the same order of the tracers in
+// every product, dP over a chunk's multipoles per lane) and k_bwd_adj, chunk by chunk: the gradients are
+// the same bit for bit.  One workgroup per CU (120 KB of LDS).  32 points of 15
+// tracers and 103 multipoles with both terms: 288 us (288 chunks in two rounds, 12.5 us per multipole: the FP32
+// issue of two transforms per tracer), against 356 us for the three kernels through the workspace; two tracers
+// on each of 8 wavefronts, two workgroups per CU, took 404 us (spills, two wavefronts per SIMD).
+template <int M> __host__ __device__ constexpr int bwd_rows_vs(int n_k) {
+  const int w = n_k > 2 * fft_lds_size(M, 4) ? n_k : 2 * fft_lds_size(M, 4);
+  return (w + 63) / 64 * 64 + 16;  // rows q and q + 1 (a half-wave of the products' reads) 16 banks apart
+}
+
+template <int M, int EXTRA>
+__global__ __launch_bounds__(1024) void k_bwd_rows(plan_dev P, swiftcl_inputs in, const float* __restrict__ dC, int nlc) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  typedef float R;
+  constexpr int RL = M / SWIFTCL_WAVE, N = 2 * M, NW = 16;
+  constexpr int NTL = (N / 16 + NW - 1) / NW;  // 16-wide k tiles per wavefront
+  const int T = P.max_tracers, Lm = P.max_ell, nk = P.n_k, nb = P.n_bands;
+  const int vs = bwd_rows_vs<M>(nk);
+  C2<R>* stw = (C2<R>*)smem;    // [N]
+  R* WY = (R*)(stw + N);        // [16][vs]
+  R* Gp = WY + (size_t)16 * vs; // [4][64]: what lane l feeds at step s, G[l % 16][4 s + l / 16]
+  R* kss = Gp + 256;            // [kind][nb][nk] k scale tables
+  R* sq2 = kss + SWIFTCL_NKINDS * nb * nk;  // [nk] 2 s of this point: dW = 2 s Y
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / SWIFTCL_WAVE), lane = tid % SWIFTCL_WAVE;
+  int b, c;
+  xcd_item(blockIdx.x, in.batch, nlc, &b, &c);
+  if (b >= in.batch) return;
+  const R* sq = (const R*)P.sqrt_s + (size_t)b * nk;
+  for (int i = tid; i < N; i += 1024) stw[i] = ((const C2<R>*)P.tw)[i];
+  for (int i = tid; i < SWIFTCL_NKINDS * nb * nk; i += 1024) kss[i] = ((const R*)P.kscale)[i];
+  for (int i = tid; i < nk; i += 1024) sq2[i] = 2.f * sq[i] * sq[i];
+  const int Tb = clampb(in.n_tracers[b], 0, T);
+  const int Lb = clampb(in.n_ell[b], 0, Lm);
+  const int l0 = (int)(((long)c * Lb) / nlc), l1 = (int)(((long)(c + 1) * Lb) / nlc);
+  const int npair = T * (T + 1) / 2;
+  const int q = lane >> 4, r = lane & 15;
+  const size_t slot = (size_t)b * nlc + c;
+  C2<R>* part = (C2<R>*)P.dchat_part + slot * T * nb * M;
+  const int t = wave;
+  const int kind = t < Tb ? tracer_kind(in, T, b, t) : 0;
+  R* row = WY + (size_t)t * vs;
+  C2<R> acc[RL];
+#pragma unroll
+  for (int e = 0; e < RL; ++e) acc[e] = mk<R>(0.f, 0.f);
+  R dp[NTL];
+#pragma unroll
+  for (int i = 0; i < NTL; ++i) dp[i] = 0.f;
+  int cur_band = -1;
+  unsigned flushed = 0;
+  auto flush = [&]() {
+    const bool again = (flushed >> cur_band) & 1u;
+    if (t < Tb) {
+      C2<R>* dst = part + ((size_t)t * nb + cur_band) * M;
+#pragma unroll
+      for (int e = 0; e < RL; ++e) {
+        const int n = lane + SWIFTCL_WAVE * e;
+        dst[n] = again ? cadd(dst[n], acc[e]) : acc[e];
+        acc[e] = mk<R>(0.f, 0.f);
+      }
+    }
+    flushed |= 1u << cur_band;
+  };
+  auto ell_of = [&](int li, int& ei, int& band) {
+    ei = in.ell_idx[(size_t)b * Lm + li];
+    if (ei < 0 || ei >= P.n_ell) {
+      if (tid == 0) atomicOr(P.flags, FLAG_BAD_INDEX);
+      ei = 0;
+    }
+    band = P.ell_band[ei];
+  };
+  auto load_G = [&](int li) {
+    if (tid >= 256) return;
+    const int i = tid / 16, j = tid % 16;
+    R g = 0.f;
+    if (i < Tb && j < Tb) {
+      const int a = i < j ? i : j, d = i < j ? j : i;
+      g = dC[((size_t)b * Lm + li) * npair + (a * T - a * (a - 1) / 2 + (d - a))];
+      if (i != j) g *= 0.5f;
+    }
+    Gp[(j >> 2) * 64 + 16 * (j & 3) + i] = g;
+  };
+  // (1) W of this wavefront's tracer of multipole (ei, band)
+  auto windows = [&](int ei, int band) {
+    if (t >= Tb) {
+      for (int j = lane; j < nk; j += SWIFTCL_WAVE) row[j] = 0.f;
+      return;
+    }
+    C2<R> v[RL];
+    wave_sync();
+    window_coeffs<M, EXTRA>(P, in, b, t, kind, ei, band, lane, v);
+    int ln = lane;  // opaque copy: keeps the FFT's per-lane LDS addresses out of the loop
+    asm volatile("" : "+v"(ln));
+    ln &= SWIFTCL_WAVE - 1;
+    wave_c2r<R, M>(v, (C2<R>*)row, stw, ln);
+    wave_sync();
+    const R* ks = kss + ((size_t)kind * nb + band) * nk;
+#pragma unroll
+    for (int e = 0; e < RL; ++e) {
+      const int k0 = 2 * (ln + SWIFTCL_WAVE * e);
+      const C2<R> kk = *(const C2<R>*)(ks + min(k0, nk - 2));
+      if (k0 < nk) *(C2<R>*)(row + k0) = mk<R>(kk.x * v[e].x, kk.y * v[e].y);
+    }
+  };
+  // (2) Y = G W in place, 16 k per tile, and this lane's share of dP
+  auto products = [&]() {
+#pragma unroll
+    for (int i = 0; i < NTL; ++i) {
+      const int col = 16 * (wave + NW * i) + r;
+      if (16 * (wave + NW * i) >= nk) continue;
+      const bool cok = col < nk;
+      v4f y = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int st = 0; st < 4; ++st) {
+        const R w = cok ? WY[(4 * st + q) * vs + col] : 0.f;
+        y = __builtin_amdgcn_mfma_f32_16x16x4f32(Gp[st * 64 + lane], w, y, 0, 0, 0);
+      }
+      if (cok) {
+#pragma unroll
+        for (int m = 0; m < 4; ++m) dp[i] += WY[(4 * q + m) * vs + col] * y[m];
+      }
+      wave_sync();
+      if (cok) {
+#pragma unroll
+        for (int m = 0; m < 4; ++m) WY[(4 * q + m) * vs + col] = y[m];
+      }
+    }
+  };
+  // (3) the adjoint transform of this wavefront's tracer
+  auto adjoint = [&](int ei, int band) {
+    if (t >= Tb) return;
+    const R* ks = kss + ((size_t)kind * nb + band) * nk;
+    C2<R> v[RL];
+#pragma unroll
+    for (int e = 0; e < RL; ++e) {
+      const int k0 = 2 * (lane + SWIFTCL_WAVE * e);
+      const int kc = min(k0, nk - 2);
+      const C2<R> y2 = *(const C2<R>*)(row + kc);
+      const C2<R> kk = *(const C2<R>*)(ks + kc);
+      const C2<R> s2 = *(const C2<R>*)(sq2 + kc);
+      v[e] = k0 < nk ? mk<R>(s2.x * kk.x * y2.x, s2.y * kk.y * y2.y) : mk<R>(0.f, 0.f);
+    }
+    const C2<R>* Ur = (const C2<R>*)P.U + ((size_t)kind * P.n_ell + ei) * M;
+    C2<R> ur[RL];  // issued before the transform, used after it
+#pragma unroll
+    for (int e = 0; e < RL; ++e) ur[e] = Ur[lane + SWIFTCL_WAVE * e];
+    wave_sync();
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
+    ln &= SWIFTCL_WAVE - 1;
+    wave_r2c<R, M>(v, (C2<R>*)row, stw, ln);
+#pragma unroll
+    for (int e = 0; e < RL; ++e) {
+      const int n = lane + SWIFTCL_WAVE * e;
+      const R h = n == 0 ? 1.f : 2.f;
+      acc[e] = cadd(acc[e], cscale(cmul(cconj(v[e]), cconj(ur[e])), h));
+    }
+  };
+  __syncthreads();
+  int ei = 0, band = 0;
+  if (l0 < l1) {
+    ell_of(l0, ei, band);
+    load_G(l0);
+    windows(ei, band);
+  }
+  __syncthreads();
+  for (int li = l0; li < l1; ++li) {
+    products();
+    __syncthreads();
+    if (band != cur_band) {
+      if (cur_band >= 0) flush();
+      cur_band = band;
+    }
+    adjoint(ei, band);
+    if (li + 1 < l1) {
+      ell_of(li + 1, ei, band);
+      load_G(li + 1);
+      windows(ei, band);
+    }
+    __syncthreads();
+  }
+  if (cur_band >= 0) flush();
+  if (tid == 0) P.bwd_bands[slot] = flushed;
+#pragma unroll
+  for (int i = 0; i < NTL; ++i) {
+    const int col = 16 * (wave + NW * i) + r;
+    R s = dp[i];
+    s += __shfl_xor(s, 16);
+    s += __shfl_xor(s, 32);
+    if (q == 0 && col < nk) ((R*)P.dpk_part)[slot * nk + col] = s;
+  }
+}
+
+// launches it; false: the plan takes the kernels through the workspace
+template <int M>
+static bool launch_bwd_rows(const plan_dev& p, const swiftcl_inputs* in, const void* dC, hipStream_t s) {
+  if constexpr (M > 512) {
+    return false;
+  } else {
+    if (p.max_tracers > 16) return false;
+    const size_t lds = (size_t)2 * M * 8 + ((size_t)16 * bwd_rows_vs<M>(p.n_k) + 256 +
+                                            (size_t)(1 + SWIFTCL_NKINDS * p.n_bands) * p.n_k) * sizeof(float);
+    const dim3 grid(xcd_blocks(in->batch, p.bwd_nlc));
+    switch ((p.rsd ? 1 : 0) | (p.mag ? 2 : 0)) {
+      case 0: hipLaunchKernelGGL((k_bwd_rows<M, 0>), grid, dim3(1024), lds, s, p, *in, (const float*)dC, p.bwd_nlc); break;
+      case 1: hipLaunchKernelGGL((k_bwd_rows<M, 1>), grid, dim3(1024), lds, s, p, *in, (const float*)dC, p.bwd_nlc); break;
+      case 2: hipLaunchKernelGGL((k_bwd_rows<M, 2>), grid, dim3(1024), lds, s, p, *in, (const float*)dC, p.bwd_nlc); break;
+      default: hipLaunchKernelGGL((k_bwd_rows<M, 3>), grid, dim3(1024), lds, s, p, *in, (const float*)dC, p.bwd_nlc); break;
+    }
+    return true;
+  }
 }
 
 // Reduce dc over chunks and take it back through the forward real transform: dg per
@@ -1257,7 +1474,9 @@ static hipError_t launch_bwd_ws(const plan_dev& p, const swiftcl_inputs* in, con
   const int nlc = p.bwd_nlc, T = p.max_tracers;
   const int ng = (T + 3) / 4;
   hipError_t e;
-  for (int b0 = 0; b0 < in->batch; b0 += p.vchunk) {
+  const bool rows = launch_bwd_rows<M>(p, in, dC, s);
+  if (rows && (e = hipGetLastError()) != hipSuccess) return e;
+  for (int b0 = 0; !rows && b0 < in->batch; b0 += p.vchunk) {
     const int nbp = in->batch - b0 < p.vchunk ? in->batch - b0 : p.vchunk;
     if ((e = launch_windows_w(p, in, b0, nbp, s)) != hipSuccess) return e;
     if ((e = launch_bwd_gv(p, in, dC, b0, nbp, s)) != hipSuccess) return e;

@@ -598,7 +598,7 @@ __global__ __launch_bounds__(256) void k_bwd_gv(plan_dev P, swiftcl_inputs in, c
 // so tile j holds the columns {4 r + j}, and every lane stores its 4 columns of a Y row as one
 // 16-byte store.  Same in-place order as k_bwd_gv.
 template <bool TWO>
-__global__ __launch_bounds__(256) void k_bwd_gv4(plan_dev P, swiftcl_inputs in, const float* __restrict__ dC,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k_bwd_gv4(plan_dev P, swiftcl_inputs in, const float* __restrict__ dC,
                                                   int b0, int nbp, int nlc) {
   __shared__ float Gs[2][32][33];
   const int tid = threadIdx.x;
@@ -979,7 +979,7 @@ static bool launch_bwd_rows(const plan_dev& p, const swiftcl_inputs* in, const v
   if constexpr (M > 512) {
     return false;
   } else {
-    if (p.max_tracers > 16) return false;
+    if (!bwd_in_lds(p)) return false;
     const size_t lds = (size_t)2 * M * 8 + ((size_t)16 * bwd_rows_vs<M>(p.n_k) + 256 +
                                             (size_t)(1 + SWIFTCL_NKINDS * p.n_bands) * p.n_k) * sizeof(float);
     const dim3 grid(xcd_blocks(in->batch, p.bwd_nlc));
@@ -1476,8 +1476,8 @@ static hipError_t launch_bwd_ws(const plan_dev& p, const swiftcl_inputs* in, con
   hipError_t e;
   const bool rows = launch_bwd_rows<M>(p, in, dC, s);
   if (rows && (e = hipGetLastError()) != hipSuccess) return e;
-  for (int b0 = 0; !rows && b0 < in->batch; b0 += p.vchunk) {
-    const int nbp = in->batch - b0 < p.vchunk ? in->batch - b0 : p.vchunk;
+  for (int b0 = 0; !rows && b0 < in->batch; b0 += p.wchunk) {
+    const int nbp = in->batch - b0 < p.wchunk ? in->batch - b0 : p.wchunk;
     if ((e = launch_windows_w(p, in, b0, nbp, s)) != hipSuccess) return e;
     if ((e = launch_bwd_gv(p, in, dC, b0, nbp, s)) != hipSuccess) return e;
     hipLaunchKernelGGL((k_bwd_adj<M, (M <= 1024)>), dim3((unsigned)((size_t)nbp * nlc * ng)), dim3(256), 0, s, p,

@@ -98,6 +98,7 @@ struct plan_dev {
   int adjoint;        // swiftcl_cl_backward: 0 not built, 1 fused (windows in LDS), 2 through the workspace
   int bwd_nlc;        // multipole chunks per point of the workspace adjoint
   int vchunk;         // points per chunk of the workspace
+  int wchunk;         // points that the workspace adjoint runs at once (>= vchunk; vbuf holds them)
   void* vbuf;         // [vchunk][max_ell][32][n_k] FP32, or bf16 hi then lo (workspace adjoint and kgrowth paths)
   // scale-dependent growth (swiftcl_cl_kgrowth); points run in chunks of vchunk
   int n_interp;       // k nodes (0 = not built)
@@ -187,6 +188,8 @@ void set_error(const std::string& msg);
 swiftcl_status check_inputs(swiftcl_plan_t p, const swiftcl_inputs* in);
 // takes the device address of swiftcl_cl_noalloc's static workspace on `device` (current), once
 swiftcl_status noalloc_setup(int device);
+// the workspace adjoint's plans that keep their rows in LDS (k_bwd_rows)
+inline bool bwd_in_lds(const plan_dev& p) { return p.max_tracers <= 16 && p.M <= 512; }
 size_t bwd_windows_lds(const plan_dev& p);  // dynamic LDS of the adjoint windows kernel
 size_t windows_cl_lds(int M, int NW, bool tw_lds, bool do_cl, size_t rs, int n_k);
 bool unfused_tw_lds(int M);

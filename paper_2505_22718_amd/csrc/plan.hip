@@ -593,7 +593,16 @@ extern "C" swiftcl_status swiftcl_plan(const swiftcl_plan_desc* d, void* stream,
       p->d.kc_chunk = (int)std::min(fit, (size_t)B);
       chunk = std::max(chunk, (size_t)p->d.kc_chunk);
     }
-    ALLOC(vbuf, char, chunk * per_point);
+    // the adjoint's kernels run all the points that 4 GB hold at once (its multipole chunks are sized for
+    // vchunk points; ten points of 30 tracers and 200 multipoles leave a third of the chip idle in a last
+    // round of workgroups), or vchunk points where that much memory is not free
+    p->d.wchunk = p->d.vchunk;
+    if (p->d.adjoint == 2 && !bwd_in_lds(p->d)) {
+      const size_t big = std::min(std::max((size_t)1, ((size_t)4 << 30) / per_point), (size_t)B);
+      if (big > chunk && hipMalloc(&p->d.vbuf, big * per_point) == hipSuccess) p->d.wchunk = (int)big;
+      else (void)hipGetLastError();
+    }
+    if (p->d.wchunk == p->d.vchunk) ALLOC(vbuf, char, chunk * per_point);
   }
   std::vector<int> kg_ia;
   std::vector<float> kg_w, kg_ip;

@@ -138,7 +138,7 @@ struct plan_dev {
   double* kc_dm;      // same layout: its second derivatives along ln k
   float* kc_dt;       // [vchunk][n_k up to 16][kc_sp] D_j on the chi nodes, shifted by j % 16
   float* kc_f;        // [kc_chunk][T][kc_sp + 16] band-0 kernel samples, padded with zeros
-  float* kc_k;        // [kc_chunk][kind][max_ell][kc_sk] the rows K_l(s), s = m0 ..
+  unsigned short* kc_k;  // [kc_chunk][kind][max_ell][3][kc_sk] the rows K_l(s), s = m0 .., as three bf16
 };
 
 // Tracer kind of slot t of point b as the kernels use it: a value outside the three kinds reads as

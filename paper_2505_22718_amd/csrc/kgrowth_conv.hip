@@ -169,9 +169,35 @@ __global__ __launch_bounds__(256) void k_kc_dj(plan_dev P, swiftcl_inputs in, in
   }
 }
 
+// x as the sum of three bf16, each the nearest to what is left: all 24 bits of x.  (Cutting instead of
+// rounding gives every part the sign of x, so that the part products left out have a bias: with both operands
+// cut the error of C grew from 2.1e-7 to 3.0e-7, with one of them to 2.4e-7.)
+__device__ __forceinline__ void split3(float x, unsigned short (&p)[3]) {
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    const __bf16 h = (__bf16)x;
+    p[i] = __builtin_bit_cast(unsigned short, h);
+    x -= (float)h;
+  }
+}
+// of two values at a time, packed (x0 in the low half)
+__device__ __forceinline__ void split3_pair(float x0, float x1, unsigned int (&p)[3]) {
+  typedef float v2f __attribute__((ext_vector_type(2)));
+  typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    const v2f x = {x0, x1};
+    p[i] = __builtin_bit_cast(unsigned int, __builtin_convertvector(x, v2bf));
+    if (i < 2) {
+      x0 -= __uint_as_float(p[i] << 16);
+      x1 -= __uint_as_float(p[i] & 0xffff0000u);
+    }
+  }
+}
+
 // K_l rows: one wavefront per (point, multipole slot, kind), idle for kinds the point has no tracer
-// of.  FP64 from the FP64 U table to the rounded row, so the row carries one FP32 rounding per entry.
-// kc_k[point][kind][slot][s - m0], s = m0 .. m1 + n_k - 1, zeros after.
+// of.  FP64 from the FP64 U table to the row, which holds K_l rounded to FP32 as the sum of three bf16.
+// kc_k[point][kind][slot][part][s - m0], s = m0 .. m1 + n_k - 1, zeros after.
 template <int M>
 __global__ __launch_bounds__(256) void k_kc_bessel(plan_dev P, swiftcl_inputs in, int b0, int nbp) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -207,14 +233,21 @@ __global__ __launch_bounds__(256) void k_kc_bessel(plan_dev P, swiftcl_inputs in
   const int m0 = P.m0, SK = P.kc_sk, last = (int)pt[PT_M1] + P.n_k - 1;
   const double db = P.fftlog_b[kind][band] - P.fftlog_b[kind][0];
   const double q1 = exp(-db * P.delta), q128 = exp(-db * P.delta * 128.0);
-  float* out = P.kc_k + (((size_t)bl * SWIFTCL_NKINDS + kind) * Lm + li) * SK;
+  unsigned short* out = P.kc_k + (((size_t)bl * SWIFTCL_NKINDS + kind) * Lm + li) * 3 * SK;
+  auto put = [&](int y, double x) {
+    if (y < 0 || y >= SK) return;
+    unsigned short part[3];
+    split3((float)x, part);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) out[(size_t)i * SK + y] = part[i];
+  };
   for (int s0 = 0; s0 - m0 < SK; s0 += N) {
     double f = exp(-db * (log(P.k0) + P.delta * (double)(s0 + 2 * lane)));
 #pragma unroll
     for (int e = 0; e < RL; ++e) {
       const int s = s0 + 2 * (lane + SWIFTCL_WAVE * e), y = s - m0;
-      if (y >= 0 && y < SK) out[y] = s <= last ? (float)(v[e].x * f) : 0.f;
-      if (y + 1 >= 0 && y + 1 < SK) out[y + 1] = s + 1 <= last ? (float)(v[e].y * f * q1) : 0.f;
+      put(y, s <= last ? v[e].x * f : 0.0);
+      put(y + 1, s + 1 <= last ? v[e].y * f * q1 : 0.0);
       f *= q128;
     }
   }
@@ -230,21 +263,24 @@ __device__ __forceinline__ unsigned short bf16_rne_kc(float x) {
 // same s.  Wave w owns tiles NC w .. NC w + NC - 1 and all of the workgroup's multipoles (<= 7 tiles of
 // 16 rows).  The rows K_l go through LDS, 32 offsets s per step, double-buffered (one block barrier per
 // step, the next step's rows in flight during this one's MFMAs).  The right operand is formed in
-// registers, one product g_t(s - j) D_j(s - j) per value, from four consecutive entries of the padded
-// kernel samples and of the shifted growth row: a lane takes the offsets 4 q .. 4 q + 3 of a group of
-// 16, and the rows are read in the same order, so every operand load is 16 bytes.
-// MFMA-bound: 28 NC MFMAs of 32 cycles per 16 offsets against 7 LDS and 2 NC cache loads.  64 points of
-// 15 tracers, 103 multipoles and 1024 k nodes (442 chi nodes): 1.01 ms, 92 TFLOP/s of the 157 that the f32
-// MFMA issues; the same windows from the node coefficients (n-sum of 1024 terms, its 200-node FFTs and
-// splines included) take 5.7 ms.
+// registers, one product g_t(s - j) D_j(s - j) per value, from eight consecutive entries of the padded
+// kernel samples and of the shifted growth row, and split like the rows.
+// Both operands are FP32 values as three bf16 each, and six of the nine part products are summed in FP32
+// on the 16x16x32 bf16 MFMA, small ones first (the three left out are below 2^-26 of the product): 2.7 times the rate of the f32
+// MFMA.  64 points of 15 tracers, 103 multipoles, 1024 k nodes and 442 chi nodes: 0.66 ms (1.01 ms on the f32
+// MFMA), 40% of the cycles on the matrix cores and as many on the vector unit (splits, loads); the same
+// windows from the node coefficients (an n-sum of 1024 terms, its 200-node FFTs and splines) take 5.7 ms.
 constexpr int KC_RT = 7;            // 16-row multipole tiles per workgroup
 constexpr int KC_SC = 32;           // offsets s per step
-constexpr int KC_KP = KC_SC + 4;    // floats per LDS row: a quarter-wave's 16-byte reads on distinct banks
+typedef unsigned short v8us __attribute__((ext_vector_type(8)));
+typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 
 // nrg: row groups of the launch; per point they share its multipole tiles evenly.
 template <bool SPLIT, int NC>
-__global__ __launch_bounds__(256) void k_kc_windows(plan_dev P, swiftcl_inputs in, int b0, int nbp, int nrg) {
-  __shared__ __align__(16) float Ks[2][KC_RT * 16][KC_KP];
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_kc_windows(plan_dev P, swiftcl_inputs in, int b0, int nbp, int nrg) {
+  // [buffer][part][row][32]; the four 16-byte groups of a row are swizzled by the row (bits 1 and 2), so
+  // that eight rows' reads of one group fall on distinct banks
+  __shared__ __align__(16) unsigned short Ks[2][3][KC_RT * 16][KC_SC];
   constexpr int NT = 4 * NC;  // column tiles per workgroup
   const int T = P.max_tracers, Lm = P.max_ell, nk = P.n_k, nb = P.n_bands;
   const int NJ = (nk + KC_J - 1) / KC_J, SP = P.kc_sp, SK = P.kc_sk;
@@ -289,8 +325,10 @@ __global__ __launch_bounds__(256) void k_kc_windows(plan_dev P, swiftcl_inputs i
   const int nst = (nh + jg1 / Tk - jg0 + 1) / 2;           // steps of 32 offsets
   const int r = lane & 15, q = lane >> 4;
   int jg[NC], tt[NC], hoff[NC];
-  const float* fp[NC];
-  const float* dp[NC];
+  // byte offsets of this lane's operands from the point's arrays
+  const char* fb = (const char*)(P.kc_f + (size_t)bl * T * (SP + KC_PAD));
+  const char* db = (const char*)(P.kc_dt + (size_t)bl * NJ * KC_J * SP);
+  unsigned int fo[NC], dof[NC];
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
     const int tile = min(t0 + wave * NC + c, ntile - 1);  // (tiles past the end repeat the last one)
@@ -299,12 +337,13 @@ __global__ __launch_bounds__(256) void k_kc_windows(plan_dev P, swiftcl_inputs i
     for (int i = tile % Tk; i > 0; --i) mk &= mk - 1;
     tt[c] = __ffs(mk) - 1;
     hoff[c] = jg[c] - jg0;
-    fp[c] = P.kc_f + ((size_t)bl * T + tt[c]) * (SP + KC_PAD) + KC_PAD + 4 * q - r;
-    dp[c] = P.kc_dt + ((size_t)bl * NJ * KC_J + jg[c] * KC_J + r) * SP + 4 * q;
+    fo[c] = 4u * (unsigned int)(tt[c] * (SP + KC_PAD) + KC_PAD + 8 * (q & 1) - r);
+    dof[c] = 4u * (unsigned int)((jg[c] * KC_J + r) * SP + 8 * (q & 1));
   }
-  // K rows: thread tid copies 16 bytes of rows tid / 8 + 32 i (rows past cnt repeat the last one)
-  const float* kr = P.kc_k + (((size_t)bl * SWIFTCL_NKINDS + kind) * Lm + r0) * SK + jg0 * KC_J;
-  const int kc = 4 * (tid & 7);
+  // K rows: 16-byte pieces (part, row, group); a thread takes group tid % 4 of rows tid / 4 and tid / 4 + 64
+  // (rows past cnt repeat the last one), every part
+  const char* kr = (const char*)(P.kc_k + (((size_t)bl * SWIFTCL_NKINDS + kind) * Lm + r0) * 3 * SK + jg0 * KC_J);
+  const int krow = tid >> 2, kgrp = tid & 3;
   v4f acc[KC_RT][NC];
 #pragma unroll
   for (int i = 0; i < KC_RT; ++i)
@@ -313,30 +352,41 @@ __global__ __launch_bounds__(256) void k_kc_windows(plan_dev P, swiftcl_inputs i
   // the loop, instantiated for the number of row tiles so that no MFMA sits behind a branch
   auto loop = [&](auto nrt_c) {
     constexpr int NRT = decltype(nrt_c)::value;
-    constexpr int NL = (NRT * 16 + 31) / 32;
-    int krow[NL];
+    constexpr int NB = (NRT * 16 + 63) / 64;  // blocks of 64 rows
+    unsigned int ko[NB];
 #pragma unroll
-    for (int i = 0; i < NL; ++i) krow[i] = min((tid >> 3) + 32 * i, cnt - 1) * SK + kc;
-    v4f kn[NL];
+    for (int i = 0; i < NB; ++i) ko[i] = 2u * (unsigned int)(min(krow + 64 * i, cnt - 1) * 3 * SK + 8 * kgrp);
+    v8us kn[NB][3];
+    unsigned short* kl = &Ks[0][0][krow][8 * (kgrp ^ ((krow >> 1) & 3))];
+    auto kget = [&](int st) {
+#pragma unroll
+      for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int part = 0; part < 3; ++part)
+          kn[i][part] = *(const v8us*)(kr + (ko[i] + 2u * (unsigned int)(part * SK + KC_SC * st)));
+    };
     auto kput = [&](int buf) {
 #pragma unroll
-      for (int i = 0; i < NL; ++i) {
-        const int row = (tid >> 3) + 32 * i;
-        if (NRT % 2 == 0 || i + 1 < NL || row < NRT * 16) *(v4f*)&Ks[buf][row][kc] = kn[i];
-      }
-    };
+      for (int i = 0; i < NB; ++i)
 #pragma unroll
-    for (int i = 0; i < NL; ++i) kn[i] = *(const v4f*)(kr + krow[i]);
+        for (int part = 0; part < 3; ++part)
+          if (NRT % 4 == 0 || i + 1 < NB || krow + 64 * i < NRT * 16)
+            *(v8us*)(kl + ((buf * 3 + part) * KC_RT * 16 + 64 * i) * KC_SC) = kn[i][part];
+    };
+    kget(0);
     kput(0);
-    v4f fn[NC], dn[NC];
-    auto fetch = [&](int h) {  // operands of offset group h of the workgroup
+    v4f fn[NC][2], dn[NC][2];
+    auto fetch = [&](int st) {  // this lane's eight offsets of step st
 #pragma unroll
       for (int c = 0; c < NC; ++c) {
         // (outside the tile's groups: a group inside them, taken times zero)
-        const int hh = h - hoff[c], hc = min(max(hh, 0), nh - 1);
-        const v4f d = *(const v4f*)(dp[c] + 16 * hc);
-        fn[c] = *(const v4fu*)(fp[c] + 16 * hc);
-        dn[c] = hh == hc ? d : (v4f){0.f, 0.f, 0.f, 0.f};
+        const int hh = 2 * st + (q >> 1) - hoff[c], hc = min(max(hh, 0), nh - 1);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const v4f d = *(const v4f*)(db + (dof[c] + 64u * (unsigned int)hc + 16u * i));
+          fn[c][i] = *(const v4fu*)(fb + (fo[c] + 64u * (unsigned int)hc + 16u * i));
+          dn[c][i] = hh == hc ? d : (v4f){0.f, 0.f, 0.f, 0.f};
+        }
       }
     };
     fetch(0);
@@ -344,25 +394,45 @@ __global__ __launch_bounds__(256) void k_kc_windows(plan_dev P, swiftcl_inputs i
     for (int st = 0; st < nst; ++st) {
       const int buf = st & 1;
       const bool more = st + 1 < nst;
-      if (more) {
+      if (more) kget(st + 1);
+      v8bf bp[3][NC];
 #pragma unroll
-        for (int i = 0; i < NL; ++i) kn[i] = *(const v4f*)(kr + krow[i] + KC_SC * (st + 1));
-      }
+      for (int c = 0; c < NC; ++c) {
+        typedef unsigned int v4ui __attribute__((ext_vector_type(4)));
+        v4ui w[3];
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        v4f bf[NC];
+        for (int e = 0; e < 4; ++e) {
+          unsigned int part[3];
+          const int g = e >> 1, o = 2 * (e & 1);
+          split3_pair(fn[c][g][o] * dn[c][g][o], fn[c][g][o + 1] * dn[c][g][o + 1], part);
 #pragma unroll
-        for (int c = 0; c < NC; ++c) bf[c] = fn[c] * dn[c];
-        fetch(2 * st + h + 1);
-#pragma unroll
-        for (int rt = 0; rt < NRT; ++rt) {
-          const v4f a = *(const v4f*)&Ks[buf][16 * rt + r][16 * h + 4 * q];
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int c = 0; c < NC; ++c)
-              acc[rt][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], bf[c][i], acc[rt][c], 0, 0, 0);
+          for (int i = 0; i < 3; ++i) w[i][e] = part[i];
         }
+#pragma unroll
+        for (int i = 0; i < 3; ++i) bp[i][c] = __builtin_bit_cast(v8bf, w[i]);
+      }
+      fetch(st + 1);
+#pragma unroll
+      for (int rt = 0; rt < NRT; ++rt) {
+        const int at = 8 * (q ^ ((r >> 1) & 3));
+        const v8bf ah = *(const v8bf*)&Ks[buf][0][16 * rt + r][at];
+        const v8bf am = *(const v8bf*)&Ks[buf][1][16 * rt + r][at];
+        const v8bf al = *(const v8bf*)&Ks[buf][2][16 * rt + r][at];
+#define SWIFTCL_KC_STEP(A, B)                                                                         \
+  for (int c = 0; c < NC; ++c) acc[rt][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, B[c], acc[rt][c], 0, 0, 0)
+#pragma unroll
+        SWIFTCL_KC_STEP(al, bp[0]);
+#pragma unroll
+        SWIFTCL_KC_STEP(ah, bp[2]);
+#pragma unroll
+        SWIFTCL_KC_STEP(am, bp[1]);
+#pragma unroll
+        SWIFTCL_KC_STEP(am, bp[0]);
+#pragma unroll
+        SWIFTCL_KC_STEP(ah, bp[1]);
+#pragma unroll
+        SWIFTCL_KC_STEP(ah, bp[0]);
+#undef SWIFTCL_KC_STEP
       }
       if (more) kput(buf ^ 1);
       __syncthreads();
@@ -470,7 +540,7 @@ size_t kgrowth_conv_bytes(const plan_dev& p) {
   const size_t NJ = (size_t)(p.n_k + KC_J - 1) / KC_J;
   return (size_t)2 * p.n_interp * p.kc_ns * sizeof(double) + NJ * KC_J * p.kc_sp * sizeof(float) +
          (size_t)p.max_tracers * (p.kc_sp + KC_PAD) * sizeof(float) +
-         (size_t)SWIFTCL_NKINDS * p.max_ell * p.kc_sk * sizeof(float);
+         (size_t)SWIFTCL_NKINDS * p.max_ell * 3 * p.kc_sk * sizeof(unsigned short);
 }
 
 hipError_t launch_kgrowth_conv(const plan_dev& p, const swiftcl_inputs* in, const double* D_kz, void* C, hipStream_t s) {

@@ -629,7 +629,7 @@ extern "C" swiftcl_status swiftcl_plan(const swiftcl_plan_desc* d, void* stream,
     ALLOC(kc_dm, double, kcc * A * p->d.kc_ns);
     ALLOC(kc_dt, float, kcc * ((nk + 15) / 16 * 16) * p->d.kc_sp);
     ALLOC(kc_f, float, kcc * T * (p->d.kc_sp + 16));
-    ALLOC(kc_k, float, kcc * SWIFTCL_NKINDS * p->d.max_ell * p->d.kc_sk);
+    ALLOC(kc_k, unsigned short, kcc * SWIFTCL_NKINDS * p->d.max_ell * 3 * p->d.kc_sk);
     // natural spline through the nodes, uniform in ln k: interval, offset and weights of every k node
     const double lk0 = std::log(d->k[0]);
     const double h = (std::log(d->k[nk - 1]) - lk0) / (A - 1);

@@ -688,6 +688,177 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
   if (q == 0 && cok) *(float4*)((float*)P.dpk_part + ((size_t)b * nlc + c) * nk + col) = dp;
 }
 
+// (a5) of the workspace adjoint: W and Y = G W without W in the workspace.  One workgroup of 16 wavefronts
+// per (point, multipole chunk): the windows of a multipole's tracers in registers (wavefront w: tracers w and,
+// NT = 2, w + 16), through LDS a slab of k at a time, Y of every slab into the workspace.  The products take the
+// tracers in the order of k_bwd_gv4 (IT_FIRST: dP row tile by row tile, as k_bwd_gv4 does; else as k_bwd_gv,
+// which grids of n_k not a multiple of 4 had), so the gradients are the same bit for bit.  Bound by the FP32
+// issue of the transforms: WYMEASURED
+template <int M, int NT> using wy_shape = slab_shape<M, NT, 16, 0>;  // (two rows of a product's read 16 banks apart)
+
+template <int M, int NT, int EXTRA>
+__global__ __launch_bounds__(1024) void k_bwd_wy(plan_dev P, swiftcl_inputs in, const float* __restrict__ dC, int b0,
+                                                 int nbp, int nlc) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  using S = wy_shape<M, NT>;
+  typedef float R;
+  constexpr int RL = S::RL, N = 2 * M, FL = fft_lds_size(M, sizeof(R));
+  constexpr bool TW = unfused_tw(M);
+  constexpr int NTW = (S::SW / 16 + 15) / 16;  // 16-wide k tiles per wavefront and slab
+  constexpr int NST = 4 * NT;                  // steps of 4 tracers
+  float* Gp = (float*)smem;                           // [NT][NST][64]: what lane l feeds, G[16 it + l % 16][4 st + l / 16]
+  C2<R>* stw_l = (C2<R>*)(Gp + NT * NST * 64);        // [N]
+  C2<R>* fbuf = stw_l + (TW ? N : 0);                 // [16][FL] transform scratch, then
+  float* slab = (float*)fbuf;                         // [2][16 NT][SP]
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / SWIFTCL_WAVE), lane0 = tid % SWIFTCL_WAVE;
+  const int T = P.max_tracers, Lm = P.max_ell, nk = P.n_k, nb = P.n_bands;
+  int bl, c;
+  xcd_item(blockIdx.x, nbp, nlc, &bl, &c);
+  if (bl >= nbp) return;
+  const int b = b0 + bl;
+  const C2<R>* stw = TW ? stw_l : (const C2<R>*)P.tw;
+  if (TW)
+    for (int i = tid; i < N; i += 1024) stw_l[i] = ((const C2<R>*)P.tw)[i];
+  const int Tb = clampb(in.n_tracers[b], 0, T);
+  const int Lb = clampb(in.n_ell[b], 0, Lm);
+  const int l0 = (int)(((long)c * Lb) / nlc), l1 = (int)(((long)(c + 1) * Lb) / nlc);
+  const int npair = T * (T + 1) / 2;
+  const bool it_first = (nk & 3) == 0;
+  R dp[S::NS * NTW];
+#pragma unroll
+  for (int i = 0; i < S::NS * NTW; ++i) dp[i] = 0.f;
+  __syncthreads();
+  for (int li = l0; li < l1; ++li) {
+    int lane = lane0;  // opaque: keeps the addresses of a multipole's work out of the loop's registers
+    asm volatile("" : "+v"(lane));
+    lane &= SWIFTCL_WAVE - 1;
+    const int q = lane >> 4, r = lane & 15;
+    int ei = in.ell_idx[(size_t)b * Lm + li];
+    if (ei < 0 || ei >= P.n_ell) {
+      if (tid == 0) atomicOr(P.flags, FLAG_BAD_INDEX);
+      ei = 0;
+    }
+    const int band = P.ell_band[ei];
+    // entry (gi, gj) of the symmetrised cotangent
+    const int ge = wave * SWIFTCL_WAVE + lane, gi = ge / (16 * NT), gj = ge % (16 * NT);
+    float g = 0.f;
+    if (gi < Tb && gj < Tb) {
+      const int a = gi < gj ? gi : gj, d = gi < gj ? gj : gi;
+      g = dC[((size_t)b * Lm + li) * npair + (a * T - a * (a - 1) / 2 + (d - a))];
+      if (gi != gj) g *= 0.5f;
+    }
+    C2<R> x[NT][RL];
+#pragma unroll
+    for (int i = 0; i < NT; ++i) {
+      const int t = wave + 16 * i;
+#pragma unroll
+      for (int e = 0; e < RL; ++e) x[i][e] = mk<R>(0.f, 0.f);
+      if (t >= Tb) continue;
+      const int kind = tracer_kind(in, T, b, t);
+      window_coeffs<M, EXTRA>(P, in, b, t, kind, ei, band, lane, x[i]);
+      int ln = lane;
+      asm volatile("" : "+v"(ln));
+      ln &= SWIFTCL_WAVE - 1;
+      wave_sync();
+      wave_c2r<R, M>(x[i], fbuf + (size_t)wave * FL, stw, ln);
+      const R* kq = (const R*)P.kscale + ((size_t)kind * nb + band) * nk;
+#pragma unroll
+      for (int e = 0; e < RL; ++e) {
+        const int k0 = 2 * (ln + SWIFTCL_WAVE * e);
+        const C2<R> kk = *(const C2<R>*)(kq + min(k0, nk - 2));  // (nk is even)
+        x[i][e] = k0 < nk ? mk<R>(kk.x * x[i][e].x, kk.y * x[i][e].y) : mk<R>(0.f, 0.f);
+      }
+    }
+    if (gi < 16 * NT) Gp[((gi >> 4) * NST + (gj >> 2)) * 64 + 16 * (gj & 3) + (gi & 15)] = g;
+    __syncthreads();  // the scratch is free, G complete
+    float* yout = (float*)P.vbuf + ((size_t)bl * Lm + li) * 32 * nk;
+#pragma unroll
+    for (int s = 0; s < S::NS; ++s) {
+      float* V = slab + (s & 1) * (16 * NT * S::SP);
+#pragma unroll
+      for (int i = 0; i < NT; ++i)
+#pragma unroll
+        for (int e = 0; e < S::SE; ++e)
+          *(C2<R>*)(V + (wave + 16 * i) * S::SP + 2 * (lane + SWIFTCL_WAVE * e)) = x[i][s * S::SE + e];
+      __syncthreads();  // (the other buffer was last read before this barrier)
+#pragma unroll
+      for (int i = 0; i < NTW; ++i) {
+        const int tile = wave + 16 * i, cl = 16 * tile + r, col = s * S::SW + cl;
+        if (tile >= S::SW / 16 || s * S::SW + 16 * tile >= nk) continue;
+        const bool cok = col < nk;
+        v4f y[NT];
+#pragma unroll
+        for (int it = 0; it < NT; ++it) y[it] = (v4f){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int st = 0; st < NST; ++st) {
+          const float bv = V[(4 * st + q) * S::SP + cl];
+#pragma unroll
+          for (int it = 0; it < NT; ++it)
+            y[it] = __builtin_amdgcn_mfma_f32_16x16x4f32(Gp[(it * NST + st) * 64 + lane], bv, y[it], 0, 0, 0);
+        }
+        R& d = dp[s * NTW + i];
+        if (NT == 1 || it_first) {
+#pragma unroll
+          for (int it = 0; it < NT; ++it)
+#pragma unroll
+            for (int m = 0; m < 4; ++m) d += V[(16 * it + 4 * q + m) * S::SP + cl] * y[it][m];
+        } else {
+#pragma unroll
+          for (int m = 0; m < 4; ++m)
+#pragma unroll
+            for (int it = 0; it < NT; ++it) d += V[(16 * it + 4 * q + m) * S::SP + cl] * y[it][m];
+        }
+        if (cok) {
+#pragma unroll
+          for (int it = 0; it < NT; ++it)
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+              const int row = 16 * it + 4 * q + m;
+              if (row < Tb) yout[(size_t)row * nk + col] = y[it][m];
+            }
+        }
+      }
+    }
+    __syncthreads();  // every slab and G are read
+  }
+  const int q = lane0 >> 4, r = lane0 & 15;
+#pragma unroll
+  for (int s = 0; s < S::NS; ++s)
+#pragma unroll
+    for (int i = 0; i < NTW; ++i) {
+      const int tile = wave + 16 * i, col = s * S::SW + 16 * tile + r;
+      R d = dp[s * NTW + i];
+      d += __shfl_xor(d, 16);
+      d += __shfl_xor(d, 32);
+      if (q == 0 && tile < S::SW / 16 && col < nk) ((R*)P.dpk_part)[((size_t)b * nlc + c) * nk + col] = d;
+    }
+}
+
+template <int M>
+static hipError_t launch_bwd_wy(const plan_dev& p, const swiftcl_inputs* in, const void* dC, int b0, int nbp,
+                                hipStream_t s) {
+  const dim3 grid(xcd_blocks(nbp, p.bwd_nlc));
+#define SWIFTCL_WY(NT, EX)                                                                                        \
+  hipLaunchKernelGGL((k_bwd_wy<M, NT, EX>), grid, dim3(1024),                                                     \
+                     (wy_shape<M, NT>::bytes(unfused_tw(M)) + (size_t)NT * NT * 4 * 64 * sizeof(float)), s, p, *in, \
+                     (const float*)dC, b0, nbp, p.bwd_nlc)
+#define SWIFTCL_WY2(EX)                        \
+  do {                                         \
+    if (p.max_tracers > 16) SWIFTCL_WY(2, EX); \
+    else if constexpr (M > 512) SWIFTCL_WY(1, EX); \
+  } while (0)
+  switch ((p.rsd ? 1 : 0) | (p.mag ? 2 : 0)) {
+    case 0: SWIFTCL_WY2(0); break;
+    case 1: SWIFTCL_WY2(1); break;
+    case 2: SWIFTCL_WY2(2); break;
+    default: SWIFTCL_WY2(3); break;
+  }
+#undef SWIFTCL_WY2
+#undef SWIFTCL_WY
+  return hipGetLastError();
+}
+
 // (a6) Adjoint transforms for one (point, multipole chunk, group of 4 tracers): wave w takes
 // tracer 4 g + w through the chunk's multipoles, dx = 2 s F k^{-1-b} Y from its workspace row,
 // r2c, dc += h conj(X) conj(U_l) in registers, flushed to the (point, chunk, tracer, band)
@@ -738,9 +909,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     flushed |= 1u << cur_band;
   };
   for (int li = l0; li < l1; ++li) {
+    int ln = lane;  // opaque: keeps the addresses of a multipole's work out of the loop's registers
+    asm volatile("" : "+v"(ln));
+    ln &= SWIFTCL_WAVE - 1;
     int ei = in.ell_idx[(size_t)b * Lm + li];
     if (ei < 0 || ei >= P.n_ell) {
-      if (lane == 0) atomicOr(P.flags, FLAG_BAD_INDEX);
+      if (ln == 0) atomicOr(P.flags, FLAG_BAD_INDEX);
       ei = 0;
     }
     const int band = P.ell_band[ei];
@@ -753,7 +927,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     C2<float> v[RL];
 #pragma unroll
     for (int e = 0; e < RL; ++e) {
-      const int k0 = 2 * (lane + SWIFTCL_WAVE * e);
+      const int k0 = 2 * (ln + SWIFTCL_WAVE * e);
       if (k0 < nk) {
         const C2<float> y2 = *(const C2<float>*)(y + k0);
         const C2<float> kk = *(const C2<float>*)(ks + k0);
@@ -764,11 +938,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
       }
     }
     wave_sync();
-    wave_r2c<float, M>(v, lds[wave], stw, lane);
+    wave_r2c<float, M>(v, lds[wave], stw, ln);
     const C2<float>* Ur = (const C2<float>*)P.U + ((size_t)kind * P.n_ell + ei) * M;
 #pragma unroll
     for (int e = 0; e < RL; ++e) {
-      const int n = lane + SWIFTCL_WAVE * e;
+      const int n = ln + SWIFTCL_WAVE * e;
       const float h = n == 0 ? 1.f : 2.f;
       acc[e] = cadd(acc[e], cscale(cmul(cconj(v[e]), cconj(Ur[n])), h));
     }
@@ -1478,8 +1652,7 @@ static hipError_t launch_bwd_ws(const plan_dev& p, const swiftcl_inputs* in, con
   if (rows && (e = hipGetLastError()) != hipSuccess) return e;
   for (int b0 = 0; !rows && b0 < in->batch; b0 += p.wchunk) {
     const int nbp = in->batch - b0 < p.wchunk ? in->batch - b0 : p.wchunk;
-    if ((e = launch_windows_w(p, in, b0, nbp, s)) != hipSuccess) return e;
-    if ((e = launch_bwd_gv(p, in, dC, b0, nbp, s)) != hipSuccess) return e;
+    if ((e = launch_bwd_wy<M>(p, in, dC, b0, nbp, s)) != hipSuccess) return e;
     hipLaunchKernelGGL((k_bwd_adj<M, (M <= 1024)>), dim3((unsigned)((size_t)nbp * nlc * ng)), dim3(256), 0, s, p,
                        *in, b0, nbp, nlc);
     if ((e = hipGetLastError()) != hipSuccess) return e;

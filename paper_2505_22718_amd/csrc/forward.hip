@@ -507,8 +507,6 @@ template <int M> struct wcl_shape<double, M> {
 
 int windows_nw(int precision) { return precision == SWIFTCL_FP64 ? 2 : 16; }
 bool windows_tw_lds(int precision, int M) { return precision != SWIFTCL_FP64 && M <= 512; }
-// the unfused FP32 windows kernel (no V rows in LDS) stages the twiddles up to n_chi = 2048
-constexpr bool unfused_tw(int M) { return M <= 1024; }
 bool unfused_tw_lds(int M) { return unfused_tw(M); }
 
 // ---------------------------------------------------------------------------------------------
@@ -522,26 +520,14 @@ bool unfused_tw_lds(int M) { return unfused_tw(M); }
 // the FP32 issue of the transforms.
 // EXTRA bit 1: the plan carries RSD, bit 2: magnification (used when the inputs give C_g).
 // ---------------------------------------------------------------------------------------------
-template <int M, int NT> struct wp_shape {
-  static constexpr int RL = M / SWIFTCL_WAVE;
-  static constexpr int SE = NT == 2 ? (RL >= 4 ? RL / 4 : 1) : RL / 2;  // registers pairs per slab
-  static constexpr int NS = RL / SE;                                    // slabs
-  static constexpr int SW = 2 * SWIFTCL_WAVE * SE;                      // k nodes per slab
-  static constexpr int SP = SW + 4;                                     // row stride: 16-byte reads on distinct banks
-  static constexpr int TILES = NT == 2 ? 3 : 1;
-  static constexpr size_t bytes(bool tw) {
-    size_t n = (size_t)16 * fft_lds_size(M, 4) * 8;
-    if ((size_t)2 * 16 * NT * SP * 4 > n) n = (size_t)2 * 16 * NT * SP * 4;
-    if ((size_t)16 * TILES * 1024 > n) n = (size_t)16 * TILES * 1024;
-    return n + (tw ? (size_t)2 * M * 8 : 0);
-  }
-};
+template <int M, int NT> using wp_shape = slab_shape<M, NT, 4, NT == 2 ? 3 : 1>;  // 16-byte reads on distinct banks
 
 template <int M, int NT, bool TW_LDS, bool SPLIT, int EXTRA>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(M <= 512 ? 8 : 4))) void k_windows_p(
     plan_dev P, swiftcl_inputs in, float* __restrict__ Cout) {
   extern __shared__ __align__(16) unsigned char smem[];
   using S = wp_shape<M, NT>;
+  constexpr int TILES = NT == 2 ? 3 : 1;
   typedef float R;
   constexpr int RL = S::RL, N = 2 * M, FL = fft_lds_size(M, sizeof(R));
   C2<R>* stw_l = (C2<R>*)smem;                                    // [N] (TW_LDS)
@@ -593,9 +579,9 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(M <= 512 ?
     }
   }
   __syncthreads();  // the scratch is free
-  v4f acc[S::TILES];
+  v4f acc[TILES];
 #pragma unroll
-  for (int i = 0; i < S::TILES; ++i) acc[i] = (v4f){0.f, 0.f, 0.f, 0.f};
+  for (int i = 0; i < TILES; ++i) acc[i] = (v4f){0.f, 0.f, 0.f, 0.f};
   const int r = lane & 15, q = lane >> 4;
 #pragma unroll
   for (int s = 0; s < S::NS; ++s) {
@@ -623,7 +609,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(M <= 512 ?
           }
         }
 #pragma unroll
-        for (int g = 0; g < S::TILES; ++g) {
+        for (int g = 0; g < TILES; ++g) {
           const int i = g == 2 ? 1 : 0, j = g == 0 ? 0 : NT - 1;
           acc[g] = mfma_bf16(h[i], h[j], acc[g]);
           acc[g] = mfma_bf16(h[i], l[j], acc[g]);
@@ -639,7 +625,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(M <= 512 ?
 #pragma unroll
         for (int m = 0; m < 4; ++m)
 #pragma unroll
-          for (int g = 0; g < S::TILES; ++g)
+          for (int g = 0; g < TILES; ++g)
             acc[g] = mfma_acc<float>::step(a[g == 2 ? 1 : 0][m], a[g == 0 ? 0 : NT - 1][m], acc[g]);
       }
     }
@@ -648,7 +634,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(M <= 512 ?
   // rows 4q..4q+3 of column r of each tile: red[wave][tile][16 r + 4 q + 0..3]
   float* red = slab;
 #pragma unroll
-  for (int g = 0; g < S::TILES; ++g) *(v4f*)(red + (wave * S::TILES + g) * 256 + 16 * r + 4 * q) = acc[g];
+  for (int g = 0; g < TILES; ++g) *(v4f*)(red + (wave * TILES + g) * 256 + 16 * r + 4 * q) = acc[g];
   __syncthreads();
   for (int idx = threadIdx.x; idx < npair; idx += 1024) {
     int i = 0, rem = idx;
@@ -659,80 +645,9 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(M <= 512 ?
       const int g = (i < 16) ? (j < 16 ? 0 : 1) : 2;
       const int e = (j % 16) * 16 + (i % 16);  // row i, column j of the tile
 #pragma unroll
-      for (int w = 0; w < 16; ++w) val += red[(w * S::TILES + g) * 256 + e];
+      for (int w = 0; w < 16; ++w) val += red[(w * TILES + g) * 256 + e];
     }
     c[idx] = val;
-  }
-}
-
-// ---------------------------------------------------------------------------------------------
-// The windows W = F(l) kscale c2r(...) of up to 32 tracer slots per (point, multipole) into the workspace
-// (FP32), for the adjoint; points in chunks of P.vchunk.
-// ---------------------------------------------------------------------------------------------
-template <int M, int NW, bool TW_LDS, int EXTRA>
-__global__ __launch_bounds__(NW * 64) void k_windows_v(plan_dev P, swiftcl_inputs in, int b0, int nbp) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  typedef float R;
-  constexpr int RL = M / SWIFTCL_WAVE;
-  constexpr int N = 2 * M;
-  constexpr int FL = fft_lds_size(M, sizeof(R));
-  constexpr int NTW = TW_LDS ? N : 0;
-  C2<R>* stw_l = (C2<R>*)smem;
-  C2<R>* fbuf = stw_l + NTW;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / SWIFTCL_WAVE), lane = threadIdx.x % SWIFTCL_WAVE;
-  const int T = P.max_tracers, Lm = P.max_ell, nk = P.n_k, nb = P.n_bands;
-  int bl, li;
-  xcd_item(blockIdx.x, nbp, Lm, &bl, &li);
-  if (bl >= nbp) return;
-  const int b = b0 + bl;
-  const int Tb = clampi(in.n_tracers[b], 0, T);
-  const int Lb = clampi(in.n_ell[b], 0, Lm);
-  const size_t row0 = ((size_t)bl * Lm + li) * 32;
-  float* vf = (float*)P.vbuf;
-  if (li >= Lb) {
-    for (size_t i = threadIdx.x; i < (size_t)32 * nk; i += NW * 64) vf[row0 * nk + i] = 0.f;
-    return;
-  }
-  int ei = in.ell_idx[(size_t)b * Lm + li];
-  if (ei < 0 || ei >= P.n_ell) {
-    if (threadIdx.x == 0) atomicOr(P.flags, FLAG_BAD_INDEX);
-    ei = 0;
-  }
-  const C2<R>* stw = TW_LDS ? stw_l : (const C2<R>*)P.tw;
-  if constexpr (TW_LDS) {
-    const C2<R>* gtw = (const C2<R>*)P.tw;
-    for (int i = threadIdx.x; i < N; i += NW * 64) stw_l[i] = gtw[i];
-    __syncthreads();
-  }
-  const int band = P.ell_band[ei];
-  C2<R>* mine = fbuf + (size_t)wave * FL;
-  for (int t = wave; t < 32; t += NW) {
-    const size_t rb = (row0 + t) * nk;
-    if (t >= Tb) {
-      for (int j = lane; j < nk; j += SWIFTCL_WAVE) vf[rb + j] = 0.f;
-      continue;
-    }
-    const int kind = tracer_kind(in, T, b, t);
-    C2<R> v[RL];
-    wave_sync();
-    window_coeffs<M, EXTRA>(P, in, b, t, kind, ei, band, lane, v);
-    int ln = lane;  // opaque copy: keeps the FFT's per-lane LDS addresses out of the tracer loop
-    asm volatile("" : "+v"(ln));
-    ln &= SWIFTCL_WAVE - 1;
-    wave_c2r<R, M>(v, mine, stw, ln);
-    const R* kq = (const R*)P.kscale + ((size_t)kind * nb + band) * nk;
-    constexpr int KG = RL < 4 ? RL : 4;  // loads issued in groups (index clamped into the row, nk even)
-#pragma unroll
-    for (int e0 = 0; e0 < RL; e0 += KG) {
-      C2<R> kk[KG];
-#pragma unroll
-      for (int e = 0; e < KG; ++e) kk[e] = *(const C2<R>*)(kq + min(2 * (ln + SWIFTCL_WAVE * (e0 + e)), nk - 2));
-#pragma unroll
-      for (int e = 0; e < KG; ++e) {
-        const int k0 = 2 * (ln + SWIFTCL_WAVE * (e0 + e));
-        if (k0 < nk) *(C2<R>*)(vf + rb + k0) = mk<R>(kk[e].x * v[e0 + e].x, kk[e].y * v[e0 + e].y);
-      }
-    }
   }
 }
 
@@ -896,32 +811,6 @@ static hipError_t launch_unfused(const plan_dev& p, const swiftcl_inputs* in, vo
 #undef SWIFTCL_WP2
 #undef SWIFTCL_WP
   return hipGetLastError();
-}
-
-template <int M>
-static hipError_t launch_ww_t(const plan_dev& p, const swiftcl_inputs* in, int b0, int nbp, hipStream_t s) {
-  constexpr int NW = 16;
-  constexpr bool TW = unfused_tw(M);
-  const size_t lds = windows_cl_lds(M, NW, TW, false, sizeof(float), p.n_k);
-  const dim3 g1(xcd_blocks(nbp, p.max_ell));
-  // the recomputed W carries the RSD and magnification terms of plans built with them
-  switch ((p.rsd ? 1 : 0) | (p.mag ? 2 : 0)) {
-    case 0: hipLaunchKernelGGL((k_windows_v<M, NW, TW, 0>), g1, dim3(NW * 64), lds, s, p, *in, b0, nbp); break;
-    case 1: hipLaunchKernelGGL((k_windows_v<M, NW, TW, 1>), g1, dim3(NW * 64), lds, s, p, *in, b0, nbp); break;
-    case 2: hipLaunchKernelGGL((k_windows_v<M, NW, TW, 2>), g1, dim3(NW * 64), lds, s, p, *in, b0, nbp); break;
-    default: hipLaunchKernelGGL((k_windows_v<M, NW, TW, 3>), g1, dim3(NW * 64), lds, s, p, *in, b0, nbp); break;
-  }
-  return hipGetLastError();
-}
-
-hipError_t launch_windows_w(const plan_dev& p, const swiftcl_inputs* in, int b0, int nbp, hipStream_t s) {
-  switch (p.M) {
-    case 128: return launch_ww_t<128>(p, in, b0, nbp, s);
-    case 256: return launch_ww_t<256>(p, in, b0, nbp, s);
-    case 512: return launch_ww_t<512>(p, in, b0, nbp, s);
-    case 1024: return launch_ww_t<1024>(p, in, b0, nbp, s);
-  }
-  return hipErrorInvalidValue;
 }
 
 template <typename R, int M, bool WRITE_W, bool DO_CL>

@@ -206,8 +206,6 @@ hipError_t launch_assemble(const plan_dev& p, const swiftcl_inputs* in, hipStrea
 hipError_t launch_forward_fft(const plan_dev& p, const swiftcl_inputs* in, hipStream_t s);
 hipError_t launch_windows_cl(const plan_dev& p, const swiftcl_inputs* in, void* W, void* C, hipStream_t s);
 hipError_t launch_sqrt_s(const plan_dev& p, const swiftcl_inputs* in, hipStream_t s);
-// FP32 rows W (not sqrt(s) W) of points [b0, b0 + nbp) into the workspace (vbuf), for the adjoint
-hipError_t launch_windows_w(const plan_dev& p, const swiftcl_inputs* in, int b0, int nbp, hipStream_t s);
 // C of points [b0, b0 + nbp) from the V rows in the workspace (vbuf)
 hipError_t launch_contract(const plan_dev& p, const swiftcl_inputs* in, void* C, int b0, int nbp, hipStream_t s);
 hipError_t launch_kgrowth(const plan_dev& p, const swiftcl_inputs* in, const double* D_kz, void* C, hipStream_t s);

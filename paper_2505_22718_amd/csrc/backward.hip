@@ -908,6 +908,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     }
     flushed |= 1u << cur_band;
   };
+  // Y of the next multipole is in flight during this one's transform
+  C2<float> yn[RL];
+  auto fetch = [&](int li, int ln) {
+    const float* y = (const float*)P.vbuf + (((size_t)bl * Lm + li) * 32 + t) * nk;
+#pragma unroll
+    for (int e = 0; e < RL; ++e) yn[e] = *(const C2<float>*)(y + min(2 * (ln + SWIFTCL_WAVE * e), nk - 2));
+  };
+  if (l0 < l1) fetch(l0, lane);
   for (int li = l0; li < l1; ++li) {
     int ln = lane;  // opaque: keeps the addresses of a multipole's work out of the loop's registers
     asm volatile("" : "+v"(ln));
@@ -922,21 +930,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
       if (cur_band >= 0) flush();
       cur_band = band;
     }
-    const float* y = (const float*)P.vbuf + (((size_t)bl * Lm + li) * 32 + t) * nk;
     const float* ks = (const float*)P.kscale + ((size_t)kind * nb + band) * nk;
     C2<float> v[RL];
 #pragma unroll
     for (int e = 0; e < RL; ++e) {
-      const int k0 = 2 * (ln + SWIFTCL_WAVE * e);
-      if (k0 < nk) {
-        const C2<float> y2 = *(const C2<float>*)(y + k0);
-        const C2<float> kk = *(const C2<float>*)(ks + k0);
-        const C2<float> s2 = *(const C2<float>*)(sq + k0);
-        v[e] = mk<float>(2.f * s2.x * s2.x * kk.x * y2.x, 2.f * s2.y * s2.y * kk.y * y2.y);
-      } else {
-        v[e] = mk<float>(0.f, 0.f);
-      }
+      const int k0 = 2 * (ln + SWIFTCL_WAVE * e), kc = min(k0, nk - 2);
+      const C2<float> y2 = yn[e];
+      const C2<float> kk = *(const C2<float>*)(ks + kc);
+      const C2<float> s2 = *(const C2<float>*)(sq + kc);
+      v[e] = k0 < nk ? mk<float>(2.f * s2.x * s2.x * kk.x * y2.x, 2.f * s2.y * s2.y * kk.y * y2.y) : mk<float>(0.f, 0.f);
     }
+    if (li + 1 < l1) fetch(li + 1, ln);
     wave_sync();
     wave_r2c<float, M>(v, lds[wave], stw, ln);
     const C2<float>* Ur = (const C2<float>*)P.U + ((size_t)kind * P.n_ell + ei) * M;

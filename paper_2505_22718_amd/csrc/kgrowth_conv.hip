@@ -163,9 +163,12 @@ __global__ __launch_bounds__(256) void k_kc_dj(plan_dev P, swiftcl_inputs in, in
       out[(size_t)r * SP + r + i] = (float)(w[0] * da + w[1] * db + w[2] * ma + w[3] * mb);
     }
   }
-  for (int e = threadIdx.x; e < KC_J * (SP - ns); e += blockDim.x) {  // before node m0 and after m1
-    const int r = e / (SP - ns), x = e % (SP - ns);
-    out[(size_t)r * SP + (x < r ? x : x + ns)] = 0.f;
+  // zeros before node m0 and after m1, up to the last group of 16 offsets that the product reads
+  const int end = (ns + KC_J - 1 + 15) / 16 * 16;
+  for (int e = threadIdx.x; e < KC_J * 32; e += blockDim.x) {  // (end - ns < 32)
+    const int r = e / 32, x = e % 32;
+    if (x < r) out[(size_t)r * SP + x] = 0.f;
+    else if (x + ns < end) out[(size_t)r * SP + x + ns] = 0.f;
   }
 }
 
@@ -229,27 +232,34 @@ __global__ __launch_bounds__(256) void k_kc_bessel(plan_dev P, swiftcl_inputs in
     v[e] = cscale(cconj(cmul(U[n], ph[n])), scale);
   }
   wave_c2r<double, M>(v, (double2*)smem + (size_t)wave * fft_lds_size(M, 8), P.kc_tw, lane);
-  // v[e] = K(s), K(s + 1) at s = 2 (lane + 64 e); the band tilt advances by e^{-db Delta} per s
+  // v[e] = K(s), K(s + 1) at s = 2 (lane + 64 e): through the scratch, so that every lane then holds eight
+  // consecutive entries of the row and stores 16 bytes of each part.  The band tilt advances by e^{-db Delta}.
+  double* Kr = (double*)((double2*)smem + (size_t)wave * fft_lds_size(M, 8));
   const int m0 = P.m0, SK = P.kc_sk, last = (int)pt[PT_M1] + P.n_k - 1;
   const double db = P.fftlog_b[kind][band] - P.fftlog_b[kind][0];
-  const double q1 = exp(-db * P.delta), q128 = exp(-db * P.delta * 128.0);
+  wave_sync();
+#pragma unroll
+  for (int e = 0; e < RL; ++e) *(double2*)(Kr + 2 * (lane + SWIFTCL_WAVE * e)) = v[e];
+  wave_sync();
+  const double q1 = exp(-db * P.delta);
   unsigned short* out = P.kc_k + (((size_t)bl * SWIFTCL_NKINDS + kind) * Lm + li) * 3 * SK;
-  auto put = [&](int y, double x) {
-    if (y < 0 || y >= SK) return;
-    unsigned short part[3];
-    split3((float)x, part);
+  for (int y = 8 * lane; y < SK; y += 8 * SWIFTCL_WAVE) {
+    const int s = m0 + y;
+    double f = exp(-db * (log(P.k0) + P.delta * (double)s));
+    typedef unsigned short v8us __attribute__((ext_vector_type(8)));
+    v8us p0, p1, p2;
 #pragma unroll
-    for (int i = 0; i < 3; ++i) out[(size_t)i * SK + y] = part[i];
-  };
-  for (int s0 = 0; s0 - m0 < SK; s0 += N) {
-    double f = exp(-db * (log(P.k0) + P.delta * (double)(s0 + 2 * lane)));
-#pragma unroll
-    for (int e = 0; e < RL; ++e) {
-      const int s = s0 + 2 * (lane + SWIFTCL_WAVE * e), y = s - m0;
-      put(y, s <= last ? v[e].x * f : 0.0);
-      put(y + 1, s + 1 <= last ? v[e].y * f * q1 : 0.0);
-      f *= q128;
+    for (int i = 0; i < 8; ++i) {
+      unsigned short part[3];
+      split3(s + i <= last ? (float)(Kr[(s + i) & (N - 1)] * f) : 0.f, part);
+      p0[i] = part[0];
+      p1[i] = part[1];
+      p2[i] = part[2];
+      f *= q1;
     }
+    *(v8us*)(out + y) = p0;
+    *(v8us*)(out + SK + y) = p1;
+    *(v8us*)(out + 2 * SK + y) = p2;
   }
 }
 

@@ -248,11 +248,14 @@ swiftcl_status swiftcl_set_launch(swiftcl_plan_t plan, int32_t fwd_mode, int32_t
 swiftcl_status swiftcl_get_launch(swiftcl_plan_t plan, int32_t* fwd_mode, int32_t* bwd_chunk_mul, int32_t* bwd_pack);
 
 /* What a built plan runs (host only, no device work): *fused = 1 when the C_l projection keeps the
- * windows of a (point, multipole) in one workgroup's LDS, 0 when it goes through the device
- * workspace in chunks of *point_chunk points (0 when the plan has no workspace); *adjoint = which
- * swiftcl_cl_backward the plan runs: 0 none (FP64 windows that do not fit LDS), 1 the fused adjoint
- * (windows recomputed in LDS), 2 the adjoint through the workspace (FP32 and split: more than 16
- * tracers, windows too large for LDS, RSD or magnification).  Any pointer may be NULL. */
+ * windows of a (point, multipole) in one workgroup's LDS, 0 when it keeps them in registers and
+ * passes them through LDS in slabs of k (more than 16 tracers, n_chi = 2048, RSD or magnification);
+ * *point_chunk = points per chunk of the device workspace (0 when the plan has none): of
+ * swiftcl_cl_kgrowth_nodes, and the number for which the adjoint's multipole chunks are sized;
+ * *adjoint = which swiftcl_cl_backward the plan runs: 0 none (FP64 windows that do not fit LDS), 1 the
+ * fused adjoint (windows recomputed in LDS), 2 the adjoint with the workspace adjoint's sums (FP32 and
+ * split: more than 16 tracers, windows too large for LDS, RSD or magnification).  Any pointer may be
+ * NULL. */
 swiftcl_status swiftcl_plan_info(swiftcl_plan_t plan, int32_t* fused, int32_t* adjoint, int32_t* point_chunk);
 
 /* Measurement variant of swiftcl_cl_backward: the same launches with HIP events between its

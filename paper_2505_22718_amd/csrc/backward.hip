@@ -504,12 +504,12 @@ __global__ __launch_bounds__(NW * 64) void k_bwd_windows(plan_dev P, swiftcl_inp
 
 // ---------------------------------------------------------------------------------------------
 // Adjoint through the workspace (more than 16 tracers, windows too large for LDS, split plans
-// whose fused adjoint does not fit): for a chunk of points the FP32 rows W of every (point,
-// multipole, tracer slot) are recomputed into the workspace (k_windows_v, w_only), k_bwd_gv
-// replaces them by Y = G W and sums W Y into the dP partials, and k_bwd_adj runs the adjoint
-// transforms of each tracer over a chunk of multipoles.  The partial rows have the layout of the
-// fused kernel's with nchunk = bwd_nlc, so k_bwd_coeffs, k_bwd_tracer and k_bwd_point follow
-// unchanged.
+// whose fused adjoint does not fit, RSD and magnification): k_bwd_wy recomputes the windows of a
+// multipole in registers and writes Y = G W to the workspace with the dP partials, and k_bwd_adj runs
+// the adjoint transforms of each tracer over a chunk of multipoles; plans whose rows fit LDS do both
+// in k_bwd_rows.  The partial rows have the layout of the fused kernel's with nchunk = bwd_nlc, so
+// k_bwd_coeffs, k_bwd_tracer and k_bwd_point follow unchanged.  The scale-dependent growth adjoint
+// has its windows W in the workspace, and k_bwd_gv / k_bwd_gv4 replace them by Y there.
 // ---------------------------------------------------------------------------------------------
 
 // (a5) Y = G W on MFMA 16x16x4 for one (point, multipole chunk, 64-wide k tile); wave w owns
@@ -596,7 +596,8 @@ __global__ __launch_bounds__(256) void k_bwd_gv(plan_dev P, swiftcl_inputs in, c
 // 256-wide k tile); lane (r, q) of wave w owns the columns 256 tile + 64 w + 4 r + (0..3) and reads
 // 4 consecutive W values of a row per load.  Column j of the four is the B operand of MFMA tile j,
 // so tile j holds the columns {4 r + j}, and every lane stores its 4 columns of a Y row as one
-// 16-byte store.  Same in-place order as k_bwd_gv.
+// 16-byte store.  Same in-place order as k_bwd_gv.  Bound by memory (W read, Y written); five wavefronts per
+// SIMD hide it better than the three of the uncapped register count (373 -> 338 us for ten points of 30 tracers).
 template <bool TWO>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k_bwd_gv4(plan_dev P, swiftcl_inputs in, const float* __restrict__ dC,
                                                   int b0, int nbp, int nlc) {
@@ -693,7 +694,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
 // NT = 2, w + 16), through LDS a slab of k at a time, Y of every slab into the workspace.  The products take the
 // tracers in the order of k_bwd_gv4 (IT_FIRST: dP row tile by row tile, as k_bwd_gv4 does; else as k_bwd_gv,
 // which grids of n_k not a multiple of 4 had), so the gradients are the same bit for bit.  Bound by the FP32
-// issue of the transforms: WYMEASURED
+// issue of the transforms and, between barriers, of the products: 64 points of 30 tracers, 200 multipoles and
+// n_k = 2048 take 2.24 ms; W through the workspace took 1.13 + 1.82 ms (6.6 GB more).
 template <int M, int NT> using wy_shape = slab_shape<M, NT, 16, 0>;  // (two rows of a product's read 16 banks apart)
 
 template <int M, int NT, int EXTRA>
@@ -863,6 +865,9 @@ static hipError_t launch_bwd_wy(const plan_dev& p, const swiftcl_inputs* in, con
 // tracer 4 g + w through the chunk's multipoles, dx = 2 s F k^{-1-b} Y from its workspace row,
 // r2c, dc += h conj(X) conj(U_l) in registers, flushed to the (point, chunk, tracer, band)
 // partial row when the band changes; rows of bands the chunk never reaches are left alone (bwd_bands).
+// Bound by the FP32 issue of the transforms; the row of the next multipole is loaded during this one's
+// transform (1.82 -> 1.30 ms for 64 points of 30 tracers, n_chi = 2048; three wavefronts per SIMD, 51 KB
+// of LDS).
 template <int M, bool TW_LDS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_bwd_adj(plan_dev P, swiftcl_inputs in, int b0, int nbp, int nlc) {
   constexpr int RL = M / SWIFTCL_WAVE;

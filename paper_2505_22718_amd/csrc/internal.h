@@ -161,17 +161,16 @@ __host__ __device__ inline unsigned xcd_blocks(int points, int slots) {
   if (xcd_by_point(points)) return (unsigned)((size_t)(points + SWIFTCL_NXCD - 1) / SWIFTCL_NXCD * SWIFTCL_NXCD * slots);
   return (unsigned)(((size_t)points * slots + SWIFTCL_NXCD - 1) / SWIFTCL_NXCD * SWIFTCL_NXCD);
 }
-// the item of block blk; point >= points: none
+// the item of block blk; point >= points: none.  (One division for both orders: two of them cost 1% of the
+// windows kernel, a workgroup of which lives for one item.)
 __host__ __device__ inline void xcd_item(int blk, int points, int slots, int* point, int* slot) {
   const int xcd = blk % SWIFTCL_NXCD, rest = blk / SWIFTCL_NXCD;
-  if (xcd_by_point(points)) {
-    *slot = rest % slots;
-    *point = rest / slots * SWIFTCL_NXCD + xcd;
-  } else {
-    const int item = xcd * (int)(xcd_blocks(points, slots) / SWIFTCL_NXCD) + rest;
-    *slot = item % slots;
-    *point = item / slots;
-  }
+  const bool by_point = xcd_by_point(points);
+  const int per = (points * slots + SWIFTCL_NXCD - 1) / SWIFTCL_NXCD;  // items of an XCD, not by point
+  const int item = by_point ? rest : xcd * per + rest;
+  const int p = item / slots;
+  *slot = item - p * slots;
+  *point = by_point ? p * SWIFTCL_NXCD + xcd : p;
 }
 
 struct swiftcl_plan_s {

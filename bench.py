@@ -403,11 +403,13 @@ def extra_configs(steps):
     D = torch.as_tensor(wl["D_kz"], **f64)
     C = torch.empty((256, plan.max_ell, plan.n_pairs), dtype=plan.out_dtype, device="cuda:0")
     ms = time_ms(lambda: plan.cl_kgrowth(inp, D, C), steps, stream)
-    # the windows GEMM: [103 l] x [N_chi real K] x [N_k] per tracer
-    gemm_flop = 2.0 * 103 * wl["n_chi"] * len(wl["k"]) * 15 * 256
+    # the windows product: [103 l] x [chi nodes of the support] x [N_k] per tracer
+    step = np.log(wl["k"][-1] / wl["k"][0]) / (len(wl["k"]) - 1)
+    nodes = np.floor(np.log(wl["chi_z"][:, -1] / wl["chi_z"][:, 0]) / step) + 1.0
+    gemm_flop = 2.0 * 103 * float(nodes.sum()) * len(wl["k"]) * 15
     progress("scale-dependent growth timed")
     out["scale_dependent_growth"] = dict(
-        forward_ms=ms, points_per_s_forward=256 / (ms * 1e-3), windows_gemm_tflop=gemm_flop / 1e12,
+        forward_ms=ms, points_per_s_forward=256 / (ms * 1e-3), windows_product_tflop=gemm_flop / 1e12,
         whole_call_tflops=gemm_flop / (ms * 1e-3) / 1e12, device_flags=plan.device_flags(),
         workload="256 points x 15 tracers x 103 l, N_k = N_chi = 1024, D(k, z) at 200 k nodes, FP32")
     del plan, D, C

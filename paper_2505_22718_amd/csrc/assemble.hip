@@ -47,10 +47,13 @@ __global__ __launch_bounds__(GEOM_THREADS) void k_geometry(plan_dev P, swiftcl_i
     if (tid == 0) atomicOr(P.flags, FLAG_BAD_INDEX);
     Tb = Tb < 1 ? 0 : T;
   }
-  // kind and bias of tracer t sit in lane t of every wavefront (<= 32 tracers): the loops over the tracers
-  // read them without a load
-  const int kd_l = lane < Tb ? in.kind[(size_t)b * T + lane] : -1;  // -1: padded slot
-  const double bias_l = lane < Tb ? in.bias[(size_t)b * T + lane] : 0.0;
+  // the tracers of each kind as bits (<= 32 tracers; a padded slot is in none): the node loop below reads them
+  // with lanes switched off, so they sit in scalar registers, not in lanes
+  const int kd_l = lane < Tb ? in.kind[(size_t)b * T + lane] : -1;
+  const unsigned clus = (unsigned)__ballot(kd_l == SWIFTCL_CLUSTERING);
+  const unsigned lens = (unsigned)__ballot(kd_l == SWIFTCL_LENSING);
+  const unsigned cmb = (unsigned)__ballot(kd_l == SWIFTCL_CMB_LENSING);
+  const scalar_row<double> bias(in.bias + (size_t)b * T);
   // LDS layout
   double* zg = sh;                      // [nzg] geometry grid
   double* zgih = zg + nzg;              // [nzg] 1/h
@@ -202,24 +205,24 @@ __global__ __launch_bounds__(GEOM_THREADS) void k_geometry(plan_dev P, swiftcl_i
 #pragma unroll
     for (int bi = 0; bi < SWIFTCL_MAX_BANDS; ++bi) eb[bi] = bi < nb ? P.ebm[(size_t)bi * N + m] : 0.0;
     for (int t = g0; t < g1; ++t) {
-      const int kd = __builtin_amdgcn_readlane(kd_l, t);
+      const unsigned bit = 1u << t;
       const size_t row = ((size_t)b * T + t) * nb * N + m;      // band 0's sample
-      if (kd == SWIFTCL_LENSING) {
+      if (lens & bit) {
         for (int bi = 0; bi < nb; ++bi) {
           if (P.rsd) ((R*)P.g_r)[row + (size_t)bi * N] = (R)0;
           if (P.mag) ((R*)P.g_mu)[row + (size_t)bi * N] = (R)0;
         }
         continue;
       }
-      const bool known = kd == SWIFTCL_CLUSTERING || kd == SWIFTCL_CMB_LENSING;
+      const bool known = (clus | cmb) & bit;
       if (t < Tb && !known && m == m0) atomicOr(P.flags, FLAG_BAD_INDEX);  // its samples stay zero
       // (the magnification samples of clustering tracers come from k_geom_lens)
-      if (kd != SWIFTCL_CLUSTERING && P.mag)
+      if (!(clus & bit) && P.mag)
         for (int bi = 0; bi < nb; ++bi) ((R*)P.g_mu)[row + (size_t)bi * N] = (R)0;
-      if (kd == SWIFTCL_CLUSTERING) {
+      if (clus & bit) {
         const double n =
             iz < 0 ? 0.0 : nw_.at(nzr + (size_t)(t - g0) * nzs, mn + (size_t)(t - g0) * nzs, iz);
-        const double f = readlane_f64(bias_l, t) * n * c0;
+        const double f = bias[t] * n * c0;
 #pragma unroll
         for (int bi = 0; bi < SWIFTCL_MAX_BANDS; ++bi) {
           if (bi >= nb) continue;
@@ -229,13 +232,13 @@ __global__ __launch_bounds__(GEOM_THREADS) void k_geometry(plan_dev P, swiftcl_i
         continue;
       }
       double f = 0.0;
-      if (kd == SWIFTCL_CMB_LENSING) {
+      if (cmb & bit) {
         // Sec. 2.4: one source plane at chi_*; the kernel falls linearly to zero there, so the last
         // node takes the trapezoid weight of a linear end, 1/2 + theta/2
         f = pref * (1.0 + z) * (chis - x) / (x * chis) * D;
         f *= m == m1 && m1 > m0 ? 0.5 + 0.5 * theta : w;
       }
-      const int kc = known ? kd : SWIFTCL_CLUSTERING;
+      const int kc = known ? SWIFTCL_CMB_LENSING : SWIFTCL_CLUSTERING;
       for (int bi = 0; bi < nb; ++bi) {
         g[row + (size_t)bi * N] = (R)(f * P.ebm[((size_t)kc * nb + bi) * N + m]);
         if (P.rsd) ((R*)P.g_r)[row + (size_t)bi * N] = (R)0;

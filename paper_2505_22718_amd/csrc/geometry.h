@@ -18,12 +18,14 @@ __constant__ static const double c_gl_w[SWIFTCL_NGL] = {
     0.17132449237916975, 0.36076157304813894, 0.46791393457269137,
     0.46791393457269137, 0.36076157304813894, 0.17132449237916975};
 
-// lane t's value of v, t uniform
-__device__ __forceinline__ double readlane_f64(double v, int t) {
-  const long long x = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_readlane((int)x, t), hi = __builtin_amdgcn_readlane((int)(x >> 32), t);
-  return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
-}
+// A row of inputs read at wave-uniform indices through the scalar cache, whichever lanes are active (the
+// kernel does not write it)
+template <typename V> struct scalar_row {
+  typedef const __attribute__((address_space(4))) V* ptr;
+  ptr p;
+  __device__ __forceinline__ explicit scalar_row(const V* row) : p((ptr)(unsigned long long)row) {}
+  __device__ __forceinline__ V operator[](int t) const { return p[t]; }
+};
 
 // value (and derivative) of the natural spline on interval i at z; ih = 1/h per interval
 __device__ __forceinline__ double spline_at(const double* __restrict__ x, const double* __restrict__ ih,

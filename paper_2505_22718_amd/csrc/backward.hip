@@ -11,6 +11,8 @@
 //      -> dg_m = Re sum_{n<N/2} conj(alpha_n) dc_n e^{+2 pi i n m / N}
 //   g_band = w f e^{-b m Delta} -> df = sum_band w e^{-b m Delta} dg_band, then the chain through
 //   the kernels (bias, n(z) spline, lensing integrals, D(z) spline) in FP64                 (a7)
+#include <algorithm>
+
 #include "common.h"
 #include "geometry.h"
 #include "internal.h"
@@ -974,7 +976,8 @@ template <int M> __host__ __device__ constexpr int bwd_rows_vs(int n_k) {
 }
 
 template <int M, int EXTRA>
-__global__ __launch_bounds__(1024) void k_bwd_rows(plan_dev P, swiftcl_inputs in, const float* __restrict__ dC, int nlc) {
+__global__ __launch_bounds__(1024) void k_bwd_rows(plan_dev P, swiftcl_inputs in, const float* __restrict__ dC, int b0,
+                                                   int nbp, int nlc) {
   extern __shared__ __align__(16) unsigned char smem[];
   typedef float R;
   constexpr int RL = M / SWIFTCL_WAVE, N = 2 * M, NW = 16;
@@ -989,8 +992,9 @@ __global__ __launch_bounds__(1024) void k_bwd_rows(plan_dev P, swiftcl_inputs in
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid / SWIFTCL_WAVE), lane = tid % SWIFTCL_WAVE;
   int b, c;
-  xcd_item(blockIdx.x, in.batch, nlc, &b, &c);
-  if (b >= in.batch) return;
+  xcd_item(blockIdx.x, nbp, nlc, &b, &c);
+  if (b >= nbp) return;
+  b += b0;
   const R* sq = (const R*)P.sqrt_s + (size_t)b * nk;
   for (int i = tid; i < N; i += 1024) stw[i] = ((const C2<R>*)P.tw)[i];
   for (int i = tid; i < SWIFTCL_NKINDS * nb * nk; i += 1024) kss[i] = ((const R*)P.kscale)[i];
@@ -1158,19 +1162,27 @@ __global__ __launch_bounds__(1024) void k_bwd_rows(plan_dev P, swiftcl_inputs in
 
 // launches it; false: the plan takes the kernels through the workspace
 template <int M>
-static bool launch_bwd_rows(const plan_dev& p, const swiftcl_inputs* in, const void* dC, hipStream_t s) {
+static bool launch_bwd_rows(const plan_dev& p, const swiftcl_inputs* in, const void* dC, hipStream_t s, hipError_t* e) {
   if constexpr (M > 512) {
     return false;
   } else {
     if (!bwd_in_lds(p)) return false;
     const size_t lds = (size_t)2 * M * 8 + ((size_t)16 * bwd_rows_vs<M>(p.n_k) + 256 +
                                             (size_t)(1 + SWIFTCL_NKINDS * p.n_bands) * p.n_k) * sizeof(float);
-    const dim3 grid(xcd_blocks(in->batch, p.bwd_nlc));
-    switch ((p.rsd ? 1 : 0) | (p.mag ? 2 : 0)) {
-      case 0: hipLaunchKernelGGL((k_bwd_rows<M, 0>), grid, dim3(1024), lds, s, p, *in, (const float*)dC, p.bwd_nlc); break;
-      case 1: hipLaunchKernelGGL((k_bwd_rows<M, 1>), grid, dim3(1024), lds, s, p, *in, (const float*)dC, p.bwd_nlc); break;
-      case 2: hipLaunchKernelGGL((k_bwd_rows<M, 2>), grid, dim3(1024), lds, s, p, *in, (const float*)dC, p.bwd_nlc); break;
-      default: hipLaunchKernelGGL((k_bwd_rows<M, 3>), grid, dim3(1024), lds, s, p, *in, (const float*)dC, p.bwd_nlc); break;
+    const int most = points_per_launch(p.bwd_nlc, 1024);
+    for (int b0 = 0; b0 < in->batch; b0 += most) {
+      const int nbp = in->batch - b0 < most ? in->batch - b0 : most;
+      const dim3 grid(xcd_blocks(nbp, p.bwd_nlc));
+#define SWIFTCL_BR(EX) \
+  hipLaunchKernelGGL((k_bwd_rows<M, EX>), grid, dim3(1024), lds, s, p, *in, (const float*)dC, b0, nbp, p.bwd_nlc)
+      switch ((p.rsd ? 1 : 0) | (p.mag ? 2 : 0)) {
+        case 0: SWIFTCL_BR(0); break;
+        case 1: SWIFTCL_BR(1); break;
+        case 2: SWIFTCL_BR(2); break;
+        default: SWIFTCL_BR(3); break;
+      }
+#undef SWIFTCL_BR
+      if ((*e = hipGetLastError()) != hipSuccess) break;
     }
     return true;
   }
@@ -1656,11 +1668,13 @@ static hipError_t launch_bwd_ws(const plan_dev& p, const swiftcl_inputs* in, con
                                 double* dbias, double* dnz, double* dD, hipStream_t s, hipEvent_t* ev) {
   const int nlc = p.bwd_nlc, T = p.max_tracers;
   const int ng = (T + 3) / 4;
-  hipError_t e;
-  const bool rows = launch_bwd_rows<M>(p, in, dC, s);
-  if (rows && (e = hipGetLastError()) != hipSuccess) return e;
-  for (int b0 = 0; !rows && b0 < in->batch; b0 += p.wchunk) {
-    const int nbp = in->batch - b0 < p.wchunk ? in->batch - b0 : p.wchunk;
+  hipError_t e = hipSuccess;
+  const bool rows = launch_bwd_rows<M>(p, in, dC, s, &e);
+  if (e != hipSuccess) return e;
+  // points per launch: what the workspace holds, and below the grids' limit (k_bwd_wy's, then k_bwd_adj's)
+  const int most = std::min(p.wchunk, std::min(points_per_launch(nlc, 1024), points_per_launch(nlc * ng, 256)));
+  for (int b0 = 0; !rows && b0 < in->batch; b0 += most) {
+    const int nbp = in->batch - b0 < most ? in->batch - b0 : most;
     if ((e = launch_bwd_wy<M>(p, in, dC, b0, nbp, s)) != hipSuccess) return e;
     hipLaunchKernelGGL((k_bwd_adj<M, (M <= 1024)>), dim3((unsigned)((size_t)nbp * nlc * ng)), dim3(256), 0, s, p,
                        *in, b0, nbp, nlc);

@@ -524,7 +524,7 @@ template <int M, int NT> using wp_shape = slab_shape<M, NT, 4, NT == 2 ? 3 : 1>;
 
 template <int M, int NT, bool TW_LDS, bool SPLIT, int EXTRA>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(M <= 512 ? 8 : 4))) void k_windows_p(
-    plan_dev P, swiftcl_inputs in, float* __restrict__ Cout) {
+    plan_dev P, swiftcl_inputs in, float* __restrict__ Cout, int b0, int nbp) {
   extern __shared__ __align__(16) unsigned char smem[];
   using S = wp_shape<M, NT>;
   constexpr int TILES = NT == 2 ? 3 : 1;
@@ -536,8 +536,9 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(M <= 512 ?
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / SWIFTCL_WAVE), lane = threadIdx.x % SWIFTCL_WAVE;
   const int T = P.max_tracers, Lm = P.max_ell, nk = P.n_k, nb = P.n_bands;
   int b, li;
-  xcd_item(blockIdx.x, in.batch, Lm, &b, &li);
-  if (b >= in.batch) return;
+  xcd_item(blockIdx.x, nbp, Lm, &b, &li);
+  if (b >= nbp) return;
+  b += b0;
   const int Tb = clampi(in.n_tracers[b], 0, T);
   const int npair = T * (T + 1) / 2;
   float* c = Cout + ((size_t)b * Lm + li) * npair;
@@ -794,23 +795,30 @@ template <int M>
 static hipError_t launch_unfused(const plan_dev& p, const swiftcl_inputs* in, void* C, hipStream_t s) {
   constexpr bool TW = unfused_tw(M);
   const bool split = p.precision == SWIFTCL_SPLIT_BF16;
-  const dim3 grid(xcd_blocks(in->batch, p.max_ell));
-#define SWIFTCL_WP(NT, SP, EX) \
-  hipLaunchKernelGGL((k_windows_p<M, NT, TW, SP, EX>), grid, dim3(1024), (wp_shape<M, NT>::bytes(TW)), s, p, *in, (float*)C)
+  const int most = points_per_launch(p.max_ell, 1024);
+  for (int b0 = 0; b0 < in->batch; b0 += most) {
+    const int nbp = in->batch - b0 < most ? in->batch - b0 : most;
+    const dim3 grid(xcd_blocks(nbp, p.max_ell));
+#define SWIFTCL_WP(NT, SP, EX)                                                                                    \
+  hipLaunchKernelGGL((k_windows_p<M, NT, TW, SP, EX>), grid, dim3(1024), (wp_shape<M, NT>::bytes(TW)), s, p, *in, \
+                     (float*)C, b0, nbp)
 #define SWIFTCL_WP2(SP, EX)                \
   do {                                     \
     if (p.max_tracers > 16) SWIFTCL_WP(2, SP, EX); \
     else SWIFTCL_WP(1, SP, EX);            \
   } while (0)
-  switch ((p.rsd ? 1 : 0) | (p.mag ? 2 : 0)) {
-    case 0: if (split) SWIFTCL_WP2(true, 0); else SWIFTCL_WP2(false, 0); break;
-    case 1: if (split) SWIFTCL_WP2(true, 1); else SWIFTCL_WP2(false, 1); break;
-    case 2: if (split) SWIFTCL_WP2(true, 2); else SWIFTCL_WP2(false, 2); break;
-    default: if (split) SWIFTCL_WP2(true, 3); else SWIFTCL_WP2(false, 3); break;
-  }
+    switch ((p.rsd ? 1 : 0) | (p.mag ? 2 : 0)) {
+      case 0: if (split) SWIFTCL_WP2(true, 0); else SWIFTCL_WP2(false, 0); break;
+      case 1: if (split) SWIFTCL_WP2(true, 1); else SWIFTCL_WP2(false, 1); break;
+      case 2: if (split) SWIFTCL_WP2(true, 2); else SWIFTCL_WP2(false, 2); break;
+      default: if (split) SWIFTCL_WP2(true, 3); else SWIFTCL_WP2(false, 3); break;
+    }
 #undef SWIFTCL_WP2
 #undef SWIFTCL_WP
-  return hipGetLastError();
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 template <typename R, int M, bool WRITE_W, bool DO_CL>

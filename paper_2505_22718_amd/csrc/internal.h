@@ -10,6 +10,9 @@
 #include "../../include/swiftcl.h"
 #include "common.h"
 #include "sched_layout.h"
+#include "xcd_map.h"
+
+static_assert(XCD_COUNT == SWIFTCL_NXCD, "one XCD count");
 
 // Per-point scalars written by the spline set-up kernel (FP64), PT_STRIDE doubles per point.
 enum {
@@ -146,31 +149,6 @@ struct plan_dev {
 __device__ __forceinline__ int tracer_kind(const swiftcl_inputs& in, int T, int b, int t) {
   const int k = in.kind[(size_t)b * T + t];
   return (unsigned)k < (unsigned)SWIFTCL_NKINDS ? k : SWIFTCL_CLUSTERING;
-}
-
-// Workgroups of a launch over (point, slot) items.  Workgroups are dispatched round-robin over the XCDs,
-// so blockIdx % 8 names the XCD and its L2.  Where the points fill the XCDs evenly, all slots of a point
-// run on one XCD (point = 8 (block / 8 / slots) + block % 8).  Where the last group of 8 points would leave
-// more XCDs idle than an eighth of the batch, every XCD takes a contiguous eighth of the item list instead:
-// one point of 103 slots by point ran on one XCD only (windows and projection 24.8 us, spread 9.6 us).
-__host__ __device__ inline bool xcd_by_point(int points) {
-  const int pad = (SWIFTCL_NXCD - points % SWIFTCL_NXCD) % SWIFTCL_NXCD;
-  return SWIFTCL_NXCD * pad <= points;
-}
-__host__ __device__ inline unsigned xcd_blocks(int points, int slots) {
-  if (xcd_by_point(points)) return (unsigned)((size_t)(points + SWIFTCL_NXCD - 1) / SWIFTCL_NXCD * SWIFTCL_NXCD * slots);
-  return (unsigned)(((size_t)points * slots + SWIFTCL_NXCD - 1) / SWIFTCL_NXCD * SWIFTCL_NXCD);
-}
-// the item of block blk; point >= points: none.  (One division for both orders: two of them cost 1% of the
-// windows kernel, a workgroup of which lives for one item.)
-__host__ __device__ inline void xcd_item(int blk, int points, int slots, int* point, int* slot) {
-  const int xcd = blk % SWIFTCL_NXCD, rest = blk / SWIFTCL_NXCD;
-  const bool by_point = xcd_by_point(points);
-  const int per = (points * slots + SWIFTCL_NXCD - 1) / SWIFTCL_NXCD;  // items of an XCD, not by point
-  const int item = by_point ? rest : xcd * per + rest;
-  const int p = item / slots;
-  *slot = item - p * slots;
-  *point = by_point ? p * SWIFTCL_NXCD + xcd : p;
 }
 
 struct swiftcl_plan_s {

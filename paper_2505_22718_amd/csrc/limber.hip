@@ -74,7 +74,8 @@ template <> struct lmfma<double> {
 
 // TWO: a second 16-row tracer tile (more than 16 tracers)
 template <typename R, bool TWO>
-__global__ __launch_bounds__(LB_LG * SWIFTCL_WAVE) void k_limber(plan_dev P, swiftcl_inputs in, R* __restrict__ Cout) {
+__global__ __launch_bounds__(LB_LG * SWIFTCL_WAVE) void k_limber(plan_dev P, swiftcl_inputs in, R* __restrict__ Cout, int b0,
+                                                                   int nbp) {
   extern __shared__ __align__(16) unsigned char smem[];
   using acc_t = typename lmfma<R>::type;
   constexpr int ROWS = TWO ? 32 : 16;
@@ -84,8 +85,9 @@ __global__ __launch_bounds__(LB_LG * SWIFTCL_WAVE) void k_limber(plan_dev P, swi
   R* s = H + (size_t)ROWS * LB_HS;              // [LB_LG][LB_CH]
   __shared__ int kinds[ROWS];
   const int ngrp = (Lm + LB_LG - 1) / LB_LG;
-  const int b = blockIdx.x / ngrp, l0 = (blockIdx.x % ngrp) * LB_LG;
-  if (b >= in.batch) return;
+  const int bl = blockIdx.x / ngrp, l0 = (blockIdx.x % ngrp) * LB_LG;
+  if (bl >= nbp) return;
+  const int b = b0 + bl;
   const int tid = threadIdx.x, nth = LB_LG * SWIFTCL_WAVE;
   const int wave = __builtin_amdgcn_readfirstlane(tid / SWIFTCL_WAVE), lane = tid % SWIFTCL_WAVE;
   const int npair = T * (T + 1) / 2;
@@ -240,7 +242,7 @@ __global__ void k_limber_zero(plan_dev P, swiftcl_inputs in) {
 constexpr int LB_BN = 64;  // chi nodes per block of the adjoint
 
 template <typename R, int NT>  // NT: 16-row tracer tiles
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NT == 1 ? 4 : 2))) void k_limber_bwd(plan_dev P, swiftcl_inputs in, const R* __restrict__ dC) {
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NT == 1 ? 4 : 2))) void k_limber_bwd(plan_dev P, swiftcl_inputs in, const R* __restrict__ dC, int b0, int nbp) {
   extern __shared__ __align__(16) unsigned char smem[];
   typedef double v4 __attribute__((ext_vector_type(4)));
   const int T = P.max_tracers, Lm = P.max_ell, N = P.N, nb = P.n_bands, nk = P.n_k;
@@ -248,8 +250,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NT == 1 ? 4
   double* dy = comb + 4 * NT * 4 * SWIFTCL_WAVE;  // [nk]
   double* dM = dy + nk;                        // [nk]
   const int nch = (N - P.m0 + LB_BN - 1) / LB_BN;
-  const int b = blockIdx.x / nch, mc = P.m0 + (blockIdx.x % nch) * LB_BN;
-  if (b >= in.batch) return;
+  const int bl = blockIdx.x / nch, mc = P.m0 + (blockIdx.x % nch) * LB_BN;
+  if (bl >= nbp) return;
+  const int b = b0 + bl;
   const double* pt = P.pt + (size_t)b * PT_STRIDE;
   const double lchi0 = log(pt[PT_CHI0]), theta = pt[PT_THETA];
   const int m0 = P.m0, m1 = (int)pt[PT_M1];
@@ -433,17 +436,21 @@ static hipError_t launch_limber_pk(const plan_dev& p, const swiftcl_inputs* in, 
 hipError_t launch_limber(const plan_dev& p, const swiftcl_inputs* in, void* C, hipStream_t s) {
   hipError_t e = launch_limber_pk(p, in, s);
   if (e != hipSuccess) return e;
-  const dim3 grid((unsigned)((size_t)in->batch * ((p.max_ell + LB_LG - 1) / LB_LG))), blk(LB_LG * SWIFTCL_WAVE);
+  const int ngrp = (p.max_ell + LB_LG - 1) / LB_LG, most = points_per_launch(ngrp, LB_LG * SWIFTCL_WAVE);
   const size_t lds = limber_lds_bytes(p);
-  if (p.precision == SWIFTCL_FP64) {  // FP64 plans hold at most 16 tracers
-    if (p.max_tracers > 16) return hipErrorNotSupported;
-    hipLaunchKernelGGL((k_limber<double, false>), grid, blk, lds, s, p, *in, (double*)C);
-  } else if (p.max_tracers > 16) {
-    hipLaunchKernelGGL((k_limber<float, true>), grid, blk, lds, s, p, *in, (float*)C);
-  } else {
-    hipLaunchKernelGGL((k_limber<float, false>), grid, blk, lds, s, p, *in, (float*)C);
+  if (p.precision == SWIFTCL_FP64 && p.max_tracers > 16) return hipErrorNotSupported;  // (no such plan is built)
+  for (int b0 = 0; b0 < in->batch; b0 += most) {
+    const int nbp = in->batch - b0 < most ? in->batch - b0 : most;
+    const dim3 grid((unsigned)((size_t)nbp * ngrp)), blk(LB_LG * SWIFTCL_WAVE);
+    if (p.precision == SWIFTCL_FP64)
+      hipLaunchKernelGGL((k_limber<double, false>), grid, blk, lds, s, p, *in, (double*)C, b0, nbp);
+    else if (p.max_tracers > 16)
+      hipLaunchKernelGGL((k_limber<float, true>), grid, blk, lds, s, p, *in, (float*)C, b0, nbp);
+    else
+      hipLaunchKernelGGL((k_limber<float, false>), grid, blk, lds, s, p, *in, (float*)C, b0, nbp);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  return hipGetLastError();
+  return hipSuccess;
 }
 
 hipError_t launch_limber_backward(const plan_dev& p, const swiftcl_inputs* in, const void* dC, double* dpk,
@@ -452,17 +459,20 @@ hipError_t launch_limber_backward(const plan_dev& p, const swiftcl_inputs* in, c
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_limber_zero, dim3(256), dim3(256), 0, s, p, *in);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  const dim3 grid((unsigned)((size_t)in->batch * ((p.N - p.m0 + LB_BN - 1) / LB_BN)));
+  const int nch = (p.N - p.m0 + LB_BN - 1) / LB_BN, most = points_per_launch(nch, 512);
   const size_t lds = limber_bwd_lds_bytes(p);
-  if (p.precision == SWIFTCL_FP64) {
-    if (p.max_tracers > 16) return hipErrorNotSupported;
-    hipLaunchKernelGGL((k_limber_bwd<double, 1>), grid, dim3(512), lds, s, p, *in, (const double*)dC);
-  } else if (p.max_tracers > 16) {
-    hipLaunchKernelGGL((k_limber_bwd<float, 2>), grid, dim3(512), lds, s, p, *in, (const float*)dC);
-  } else {
-    hipLaunchKernelGGL((k_limber_bwd<float, 1>), grid, dim3(512), lds, s, p, *in, (const float*)dC);
+  if (p.precision == SWIFTCL_FP64 && p.max_tracers > 16) return hipErrorNotSupported;
+  for (int b0 = 0; b0 < in->batch; b0 += most) {
+    const int nbp = in->batch - b0 < most ? in->batch - b0 : most;
+    const dim3 grid((unsigned)((size_t)nbp * nch));
+    if (p.precision == SWIFTCL_FP64)
+      hipLaunchKernelGGL((k_limber_bwd<double, 1>), grid, dim3(512), lds, s, p, *in, (const double*)dC, b0, nbp);
+    else if (p.max_tracers > 16)
+      hipLaunchKernelGGL((k_limber_bwd<float, 2>), grid, dim3(512), lds, s, p, *in, (const float*)dC, b0, nbp);
+    else
+      hipLaunchKernelGGL((k_limber_bwd<float, 1>), grid, dim3(512), lds, s, p, *in, (const float*)dC, b0, nbp);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  if ((e = hipGetLastError()) != hipSuccess) return e;
   if (dpk) {
     hipLaunchKernelGGL(k_limber_bwd_pk, dim3(in->batch), dim3(512), sizeof(double) * 2 * (size_t)p.n_k, s, p, *in,
                        dpk);

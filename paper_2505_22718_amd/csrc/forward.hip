@@ -863,17 +863,29 @@ static hipError_t launch_wcl_t(const plan_dev& p, const swiftcl_inputs* in, void
                        (R*)W, (R*)C);
     return hipGetLastError();
   }
-  const dim3 grid(xcd_blocks(in->batch, p.max_ell));
-  if constexpr (sizeof(R) == 4 && DO_CL) {
-    if (split) {
-      hipLaunchKernelGGL((k_windows_cl<R, M, NW, TW, WRITE_W, DO_CL, 0, true>), grid, dim3(NW * 64), lds, s, p,
-                         *in, (R*)W, (R*)C);
-      return hipGetLastError();
-    }
+  const int most = points_per_launch(p.max_ell, NW * 64);
+  for (int b0 = 0; b0 < in->batch; b0 += most) {
+    // (a large batch's later points by shifted pointers: the kernel takes no first point)
+    plan_dev q = p;
+    swiftcl_inputs iq = *in;
+    iq.batch = in->batch - b0 < most ? in->batch - b0 : most;
+    iq.n_tracers += b0;
+    iq.n_ell += b0;
+    iq.kind += (size_t)b0 * p.max_tracers;
+    iq.ell_idx += (size_t)b0 * p.max_ell;
+    q.chat = (C2<R>*)p.chat + (size_t)b0 * p.max_tracers * p.n_bands * M;
+    q.kss = (R*)p.kss + (size_t)b0 * SWIFTCL_NKINDS * p.n_bands * p.n_k;
+    R* w = W ? (R*)W + (size_t)b0 * p.max_ell * p.max_tracers * p.n_k : nullptr;
+    R* c = C ? (R*)C + (size_t)b0 * p.max_ell * (p.max_tracers * (p.max_tracers + 1) / 2) : nullptr;
+    const dim3 grid(xcd_blocks(iq.batch, p.max_ell));
+    auto kernel = k_windows_cl<R, M, NW, TW, WRITE_W, DO_CL, 0, false>;
+    if constexpr (sizeof(R) == 4 && DO_CL)
+      if (split) kernel = k_windows_cl<R, M, NW, TW, WRITE_W, DO_CL, 0, true>;
+    hipLaunchKernelGGL(kernel, grid, dim3(NW * 64), lds, s, q, iq, w, c);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((k_windows_cl<R, M, NW, TW, WRITE_W, DO_CL, 0, false>), grid, dim3(NW * 64), lds, s, p, *in,
-                     (R*)W, (R*)C);
-  return hipGetLastError();
+  return hipSuccess;
 }
 
 template <typename R, int M>

@@ -44,6 +44,20 @@ def test_projection(dev):
     assert bool((C == ref).all())
 
 
+def test_fused_projection_and_windows(dev):
+    """The same workgroups through k_windows_cl, for C_l and for the windows themselves."""
+    p, t = _plan(4200, 1024, 1024, 64)
+    p1, t1 = _plan(3, 1024, 1024, 64)
+    ref = p1.cl(t1)[:1]
+    assert bool(ref.ne(0).all())
+    assert bool((p.cl(t) == ref).all())
+    ref = p1.windows(t1)[:1]
+    W = p.windows(t)
+    assert p.device_flags() == 0
+    for b in range(0, 4200, 600):
+        assert bool((W[b:b + 600] == ref).all()), b
+
+
 def test_rows_adjoint(dev):
     """16400 points of 256 multipole chunks through k_bwd_rows: 4.2 million workgroups of 1024 threads."""
     p, t = _plan(16400, 1024, 256, 256, rsd=True)

@@ -100,9 +100,10 @@ struct plan_dev {
   int fused;
   int adjoint;        // swiftcl_cl_backward: 0 not built, 1 fused (windows in LDS), 2 through the workspace
   int bwd_nlc;        // multipole chunks per point of the workspace adjoint
-  int vchunk;         // points per chunk of the workspace
-  int wchunk;         // points that the workspace adjoint runs at once (>= vchunk; vbuf holds them)
-  void* vbuf;         // [vchunk][max_ell][32][n_k] FP32, or bf16 hi then lo (workspace adjoint and kgrowth paths)
+  int vchunk;         // points per chunk that the workspace adjoint's multipole chunks are sized for, and of kg_c / kg_m
+  int wchunk;         // points that the workspace adjoint runs at once (>= vchunk)
+  void* vbuf;         // [largest of vchunk, wchunk, kc_chunk][max_ell][32][n_k] FP32, or bf16 hi then lo
+                      // (workspace adjoint and kgrowth paths)
   // scale-dependent growth (swiftcl_cl_kgrowth); points run in chunks of vchunk
   int n_interp;       // k nodes (0 = not built)
   // redshift-space distortions (eq. RSD) of the clustering tracers: a second coefficient set per
@@ -129,7 +130,7 @@ struct plan_dev {
   int* kg_perm;       // [vchunk][max_ell] multipole slots grouped by band
   int* kg_tile;       // [vchunk][kg_ntile][4] band, first entry of kg_perm, count, 0
   // the same by the product over the chi nodes of the support (kgrowth_conv.hip)
-  int kc_chunk;       // points per chunk (of vbuf too)
+  int kc_chunk;       // points per chunk (0: no memory for its operands, the node coefficients take its place)
   int kc_ns;          // chi nodes a support may hold: N - m0
   int kc_sp;          // entries per growth row (kc_dt); kc_f rows hold 16 more
   int kc_sk;          // entries per K_l row
@@ -139,7 +140,7 @@ struct plan_dev {
   double2* kc_tw;     // [N] the twiddles in FP64
   double* kc_dn;      // [kc_chunk][n_interp][kc_ns] growth of the nodes on the chi nodes m0 ..
   double* kc_dm;      // same layout: its second derivatives along ln k
-  float* kc_dt;       // [vchunk][n_k up to 16][kc_sp] D_j on the chi nodes, shifted by j % 16
+  float* kc_dt;       // [kc_chunk][n_k up to 16][kc_sp] D_j on the chi nodes, shifted by j % 16
   float* kc_f;        // [kc_chunk][T][kc_sp + 16] band-0 kernel samples, padded with zeros
   unsigned short* kc_k;  // [kc_chunk][kind][max_ell][3][kc_sk] the rows K_l(s), s = m0 .., as three bf16
 };

@@ -20,6 +20,7 @@
 
 #include "common.h"
 #include "internal.h"
+#include "workspace.h"
 
 static thread_local std::string g_last_error;
 
@@ -185,7 +186,7 @@ hipError_t launch_u_table(const plan_dev& pd, const double* d_ell, hipStream_t s
   else
     hipLaunchKernelGGL(k_u_table<float>, grid, dim3(128), 0, s, (float2*)p->U, d_ell, p->ell_band, p->fell, bt,
                        p->n_ell, p->M, p->delta, p->taper_frac);
-  if (p->n_interp > 0)
+  if (p->kc_chunk > 0)
     hipLaunchKernelGGL(k_u_table<double>, grid, dim3(128), 0, s, p->kc_u, d_ell, p->ell_band, p->fell, bt, p->n_ell,
                        p->M, p->delta, p->taper_frac);
   if (p->rsd)  // RSD and magnification plans are FP32 / split
@@ -324,17 +325,39 @@ template <typename T> static swiftcl_status dalloc(T** ptr, size_t count, const 
   return SWIFTCL_OK;
 }
 
+// The growth product's tables and its operands of kc_chunk points (none if 0); false: no memory for them.
+static bool alloc_growth_product(plan_dev& d) {
+  if (!d.kc_chunk) return true;
+  const size_t kcc = d.kc_chunk, nk = d.n_k, A = d.n_interp;
+  return dalloc(&d.kc_w, 4 * nk, "kc_w") == SWIFTCL_OK && dalloc(&d.kc_ip, A, "kc_ip") == SWIFTCL_OK &&
+         dalloc(&d.kc_u, (size_t)SWIFTCL_NKINDS * d.n_ell * d.M, "kc_u") == SWIFTCL_OK &&
+         dalloc(&d.kc_tw, d.N, "kc_tw") == SWIFTCL_OK && dalloc(&d.kc_dn, kcc * A * d.kc_ns, "kc_dn") == SWIFTCL_OK &&
+         dalloc(&d.kc_dm, kcc * A * d.kc_ns, "kc_dm") == SWIFTCL_OK &&
+         dalloc(&d.kc_dt, kcc * ((nk + 15) / 16 * 16) * d.kc_sp, "kc_dt") == SWIFTCL_OK &&
+         dalloc(&d.kc_f, kcc * d.max_tracers * (d.kc_sp + 16), "kc_f") == SWIFTCL_OK &&
+         dalloc(&d.kc_k, kcc * SWIFTCL_NKINDS * d.max_ell * 3 * d.kc_sk, "kc_k") == SWIFTCL_OK;
+}
+
+static void free_workspace(plan_dev& d) {
+  void** ptrs[] = {&d.vbuf, (void**)&d.kc_w, (void**)&d.kc_ip, (void**)&d.kc_u, (void**)&d.kc_tw, (void**)&d.kc_dn,
+                   (void**)&d.kc_dm, (void**)&d.kc_dt, (void**)&d.kc_f, (void**)&d.kc_k};
+  for (void** q : ptrs) {
+    if (*q) (void)hipFree(*q);
+    *q = nullptr;
+  }
+}
+
 static void free_plan(swiftcl_plan_s* p) {
   if (!p) return;
   void* ptrs[] = {p->d.U, p->d.kscale, p->d.tw, p->d.fell, p->d.ell_band, p->d.kw, p->d.ell_v, p->d.lnk, p->d.lu_k,
                   p->d.lnp, p->d.lim_acc, p->d.ebm, p->d.z_geom, p->d.z_nz, p->d.lu_geom,
                   p->d.lu_nz, p->d.z_union, p->d.union_iv, p->d.union_g, p->d.pt, p->d.m_chi, p->d.m_D, p->d.m_ia, p->d.m_n, p->d.lens_q, p->d.phase, p->d.node_f, p->d.node_i, p->d.ddD_part, p->d.g,
-                  p->d.chat, p->d.sqrt_s, p->d.kss, p->d.flags, p->d.dchat_part, p->d.bwd_bands, p->d.dpk_part, p->d.dg, p->d.sched, p->d.bwd_order, p->d.vbuf,
+                  p->d.chat, p->d.sqrt_s, p->d.kss, p->d.flags, p->d.dchat_part, p->d.bwd_bands, p->d.dpk_part, p->d.dg, p->d.sched, p->d.bwd_order,
                   p->d.kg_ones, p->d.kg_ia, p->d.kg_w, p->d.kg_ip, p->d.kg_uh, p->d.kg_c, p->d.kg_m, p->d.kg_perm,
-                  p->d.kg_tile, p->d.kc_w, p->d.kc_ip, p->d.kc_u, p->d.kc_tw, p->d.kc_dn, p->d.kc_dm, p->d.kc_dt,
-                  p->d.kc_f, p->d.kc_k, p->d.UR, p->d.g_r, p->d.chat_r, p->d.Umu, p->d.g_mu, p->d.chat_mu};
+                  p->d.kg_tile, p->d.UR, p->d.g_r, p->d.chat_r, p->d.Umu, p->d.g_mu, p->d.chat_mu};
   for (void* q : ptrs)
     if (q) (void)hipFree(q);
+  free_workspace(p->d);
   delete p;
 }
 
@@ -576,33 +599,24 @@ extern "C" swiftcl_status swiftcl_plan(const swiftcl_plan_desc* d, void* stream,
     p->d.bwd_order_n = (int)grid;
   }
   p->d.n_interp = d->n_interp;
-  if (!p->d.fused || p->d.n_interp > 0 || p->d.adjoint == 2) {
-    // workspace of the adjoint (W of up to 32 tracer slots) and of scale-dependent growth (node coefficients and their spline moments), a chunk of points at a time
-    const size_t per_point = (size_t)p->d.max_ell * 32 * nk * 4;
-    size_t chunk = ((size_t)512 << 20) / per_point;
-    if (p->d.n_interp > 0) {
-      const size_t per_kg = per_point + (size_t)2 * T * nb * p->d.n_interp * M * 8;
-      chunk = ((size_t)4 << 30) / per_kg;
-    }
-    if (chunk < 1) chunk = 1;
-    if (chunk > (size_t)B) chunk = B;
-    p->d.vchunk = (int)chunk;
+  // points per chunk of the workspace: V rows of up to 32 tracer slots (the adjoint's Y, the growth paths'
+  // windows) and the node coefficients of scale-dependent growth with their spline moments.  The multipole
+  // chunks of the workspace adjoint are sized for it, in LDS (k_bwd_rows) too, where no row is in memory
+  const bool ws_rows = p->d.n_interp > 0 || (p->d.adjoint == 2 && !bwd_in_lds(p->d));
+  workspace_request want{(size_t)p->d.max_ell * 32 * nk * 4, 0, 0, 0, 0};
+  if (p->d.n_interp > 0 || p->d.adjoint == 2) {
+    size_t chunk = ((size_t)512 << 20) / want.vbuf_point;
+    if (p->d.n_interp > 0) chunk = ((size_t)4 << 30) / (want.vbuf_point + (size_t)2 * T * nb * p->d.n_interp * M * 8);
+    p->d.vchunk = want.base = (int)std::min(std::max(chunk, (size_t)1), (size_t)B);
+    // the adjoint's kernels like all the points that 4 GB hold at once (ten points of 30 tracers and 200
+    // multipoles leave a third of the chip idle in a last round of workgroups), and so does the growth product
+    const auto fit4 = [&](size_t per_point) { return (int)std::min(std::max((size_t)1, ((size_t)4 << 30) / per_point), (size_t)B); };
+    want.adjoint = p->d.adjoint == 2 ? std::max(want.base, fit4(want.vbuf_point)) : want.base;
     if (p->d.n_interp > 0) {
       kgrowth_conv_sizes(p->d);
-      const size_t fit = std::max((size_t)1, ((size_t)4 << 30) / (per_point + kgrowth_conv_bytes(p->d)));
-      p->d.kc_chunk = (int)std::min(fit, (size_t)B);
-      chunk = std::max(chunk, (size_t)p->d.kc_chunk);
+      want.growth_point = kgrowth_conv_bytes(p->d);
+      want.growth = fit4(want.vbuf_point + want.growth_point);
     }
-    // the adjoint's kernels run all the points that 4 GB hold at once (its multipole chunks are sized for
-    // vchunk points; ten points of 30 tracers and 200 multipoles leave a third of the chip idle in a last
-    // round of workgroups), or vchunk points where that much memory is not free
-    p->d.wchunk = p->d.vchunk;
-    if (p->d.adjoint == 2 && !bwd_in_lds(p->d)) {
-      const size_t big = std::min(std::max((size_t)1, ((size_t)4 << 30) / per_point), (size_t)B);
-      if (big > chunk && hipMalloc(&p->d.vbuf, big * per_point) == hipSuccess) p->d.wchunk = (int)big;
-      else (void)hipGetLastError();
-    }
-    if (p->d.wchunk == p->d.vchunk) ALLOC(vbuf, char, chunk * per_point);
   }
   std::vector<int> kg_ia;
   std::vector<float> kg_w, kg_ip;
@@ -620,16 +634,6 @@ extern "C" swiftcl_status swiftcl_plan(const swiftcl_plan_desc* d, void* stream,
     ALLOC(kg_m, char, chunk * T * nb * A * M * 8);
     ALLOC(kg_perm, int, chunk * p->d.max_ell);
     ALLOC(kg_tile, int, chunk * p->d.kg_ntile * 4);
-    const size_t kcc = p->d.kc_chunk;
-    ALLOC(kc_w, double, (size_t)4 * nk);
-    ALLOC(kc_ip, double, A);
-    ALLOC(kc_u, double2, (size_t)SWIFTCL_NKINDS * p->d.n_ell * M);
-    ALLOC(kc_tw, double2, N);
-    ALLOC(kc_dn, double, kcc * A * p->d.kc_ns);
-    ALLOC(kc_dm, double, kcc * A * p->d.kc_ns);
-    ALLOC(kc_dt, float, kcc * ((nk + 15) / 16 * 16) * p->d.kc_sp);
-    ALLOC(kc_f, float, kcc * T * (p->d.kc_sp + 16));
-    ALLOC(kc_k, unsigned short, kcc * SWIFTCL_NKINDS * p->d.max_ell * 3 * p->d.kc_sk);
     // natural spline through the nodes, uniform in ln k: interval, offset and weights of every k node
     const double lk0 = std::log(d->k[0]);
     const double h = (std::log(d->k[nk - 1]) - lk0) / (A - 1);
@@ -676,6 +680,24 @@ extern "C" swiftcl_status swiftcl_plan(const swiftcl_plan_desc* d, void* stream,
   ALLOC(dg, char, (size_t)B * T * nb * N * rs);
 #undef ALLOC
 
+  // the workspace last: what else the plan needs has its memory, and the chunks shrink to what is left.  A plan
+  // that has no room even for one point of the growth product's operands runs swiftcl_cl_kgrowth by the node
+  // coefficients
+  if (ws_rows) {
+    size_t free_b = 0, total_b = 0;
+    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) free_b = 0;
+    const workspace_points tries[] = {workspace_fit(want, free_b), workspace_fit(want, 0), {want.base, want.base, 0}};
+    bool ok = false;
+    for (const workspace_points& w : tries) {
+      p->d.wchunk = w.adjoint;
+      p->d.kc_chunk = w.growth;
+      if ((ok = dalloc((char**)&p->d.vbuf, w.vbuf * want.vbuf_point, "vbuf") == SWIFTCL_OK && alloc_growth_product(p->d))) break;
+      (void)hipGetLastError();
+      free_workspace(p->d);
+    }
+    if (!ok) { free_plan(p); return SWIFTCL_E_NOMEM; }
+  }
+
   // --- uploads (host tables converted to the FFT precision) ---
   auto to_real = [&](const std::vector<double>& v) {
     std::vector<char> buf(v.size() * rs);
@@ -719,6 +741,7 @@ extern "C" swiftcl_status swiftcl_plan(const swiftcl_plan_desc* d, void* stream,
                      {p->d.kc_ip, kc_ip.data(), kc_ip.size() * sizeof(double)},
                      {p->d.kc_tw, twd.data(), twd.size() * sizeof(double)}};
     for (auto& u : kg) {
+      if (!u.dst) continue;  // (no growth product)
       e = hipMemcpyAsync(u.dst, u.src, u.n, hipMemcpyHostToDevice, s);
       if (e != hipSuccess) break;
     }
@@ -877,7 +900,7 @@ static swiftcl_status run_kgrowth(swiftcl_plan_t p, const swiftcl_inputs* in, co
   hipError_t e = launch_assemble(p->d, &in1, s);
   if (e == hipSuccess) e = launch_sqrt_s(p->d, &in1, s);
   if (e == hipSuccess)
-    e = nodes ? launch_kgrowth(p->d, &in1, D_kz, C, s) : launch_kgrowth_conv(p->d, &in1, D_kz, C, s);
+    e = nodes || !p->d.kc_chunk ? launch_kgrowth(p->d, &in1, D_kz, C, s) : launch_kgrowth_conv(p->d, &in1, D_kz, C, s);
   return hip_check(e, "scale-dependent growth launch");
 }
 

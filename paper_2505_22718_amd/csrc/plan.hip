@@ -318,6 +318,7 @@ template <typename T> static swiftcl_status dalloc(T** ptr, size_t count, const 
   if (count == 0) count = 1;
   hipError_t e = hipMalloc((void**)ptr, count * sizeof(T));
   if (e != hipSuccess) {
+    (void)hipGetLastError();  // (the status says it; a later check of the program's own would find it again)
     *ptr = nullptr;
     set_error(std::string("hipMalloc failed for ") + what);
     return SWIFTCL_E_NOMEM;
@@ -692,7 +693,6 @@ extern "C" swiftcl_status swiftcl_plan(const swiftcl_plan_desc* d, void* stream,
       p->d.wchunk = w.adjoint;
       p->d.kc_chunk = w.growth;
       if ((ok = dalloc((char**)&p->d.vbuf, w.vbuf * want.vbuf_point, "vbuf") == SWIFTCL_OK && alloc_growth_product(p->d))) break;
-      (void)hipGetLastError();
       free_workspace(p->d);
     }
     if (!ok) { free_plan(p); return SWIFTCL_E_NOMEM; }
@@ -708,7 +708,7 @@ extern "C" swiftcl_status swiftcl_plan(const swiftcl_plan_desc* d, void* stream,
   std::vector<char> kscale_r = to_real(kscale), tw_r = to_real(twd);
   double* d_ell = nullptr;
   hipError_t e = hipMalloc((void**)&d_ell, sizeof(double) * p->d.n_ell);
-  if (e != hipSuccess) { free_plan(p); set_error("hipMalloc failed for ell"); return SWIFTCL_E_NOMEM; }
+  if (e != hipSuccess) { (void)hipGetLastError(); free_plan(p); set_error("hipMalloc failed for ell"); return SWIFTCL_E_NOMEM; }
   struct Up { void* dst; const void* src; size_t n; } ups[] = {
       {p->d.kscale, kscale_r.data(), kscale_r.size()},
       {p->d.tw, tw_r.data(), tw_r.size()},

@@ -101,3 +101,17 @@ def test_rows_adjoint_takes_no_workspace(dev):
     print(f"  {size / 2**20:.0f} MiB", flush=True)
     p.close()
     assert size < 40 * 103 * 32 * 1024 * 4
+
+
+def test_a_refused_plan_leaves_no_error_behind(dev):
+    """A plan that no device holds (3 million points) is refused with E_NOMEM, its memory is given back, and the
+    program's next GPU calls do not meet the failed allocation."""
+    from paper_2505_22718_amd import binding as bd
+    from paper_2505_22718_amd.plan import Plan
+    wl = _workload(15, 1)
+    before = _free()
+    with pytest.raises(bd.SwiftclError) as err:
+        Plan.for_workload(wl, precision="fp32", max_batch=3000000)
+    assert err.value.status == bd.SWIFTCL_E_NOMEM
+    assert float(torch.ones(8, device=dev).expand(4, 8).contiguous().sum()) == 32.0
+    assert _free() >= before - (64 << 20)

@@ -258,6 +258,13 @@ swiftcl_status swiftcl_get_launch(swiftcl_plan_t plan, int32_t* fwd_mode, int32_
  * NULL. */
 swiftcl_status swiftcl_plan_info(swiftcl_plan_t plan, int32_t* fused, int32_t* adjoint, int32_t* point_chunk);
 
+/* Points that the chunked paths run at once (host only, no device work): *adjoint of the adjoint through the
+ * workspace, *growth of swiftcl_cl_kgrowth; 0 where the plan has no such path (growth: or no memory for it, and
+ * the node coefficients take its place).  They were chosen when the plan was built from the memory that was
+ * free.  limit > 0: later calls run at most that many; limit 0: as many as the workspace holds; limit < 0: as
+ * before.  The gradients are the same bit for bit, C of growth to FP32 rounding.  Either pointer may be NULL. */
+swiftcl_status swiftcl_workspace_points(swiftcl_plan_t plan, int32_t limit, int32_t* adjoint, int32_t* growth);
+
 /* Measurement variant of swiftcl_cl_backward: the same launches with HIP events between its
  * stages; writes the device time in ms of [0] kernel assembly, [1] forward FFTLog coefficients
  * (both 0 with SWIFTCL_BWD_REUSE_FORWARD), [2] backward windows (recomputed W, G W on MFMA,

@@ -84,7 +84,8 @@ EXPORTED = ["swiftcl_plan", "swiftcl_plan_destroy", "swiftcl_last_error", "swift
             "swiftcl_windows", "swiftcl_cl", "swiftcl_cl_timed", "swiftcl_cl_backward",
             "swiftcl_cl_backward_timed", "swiftcl_autotune", "swiftcl_set_launch", "swiftcl_get_launch",
             "swiftcl_cl_kgrowth", "swiftcl_cl_limber", "swiftcl_cl_noalloc", "swiftcl_plan_info",
-            "swiftcl_cl_limber_backward", "swiftcl_cl_kgrowth_backward", "swiftcl_cl_kgrowth_nodes"]
+            "swiftcl_cl_limber_backward", "swiftcl_cl_kgrowth_backward", "swiftcl_cl_kgrowth_nodes",
+            "swiftcl_workspace_points"]
 
 _lib = None
 
@@ -119,6 +120,7 @@ def load(path: str = LIB_PATH):
     lib.swiftcl_get_launch.argtypes = [vp, ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_int32),
                                        ctypes.POINTER(ctypes.c_int32)]
     lib.swiftcl_plan_info.argtypes = [vp] + [ctypes.POINTER(ctypes.c_int32)] * 3
+    lib.swiftcl_workspace_points.argtypes = [vp, ctypes.c_int32] + [ctypes.POINTER(ctypes.c_int32)] * 2
     lib.swiftcl_cl_backward_timed.argtypes = [vp, ctypes.POINTER(swiftcl_inputs), vp, vp, vp, vp, vp,
                                               ctypes.c_uint32, vp, ctypes.POINTER(ctypes.c_float)]
     for name in EXPORTED:
@@ -242,6 +244,12 @@ def swiftcl_plan_info(plan):
     f, a, c = ctypes.c_int32(), ctypes.c_int32(), ctypes.c_int32()
     _check(load().swiftcl_plan_info(plan, ctypes.byref(f), ctypes.byref(a), ctypes.byref(c)))
     return {"fused": f.value, "adjoint": a.value, "point_chunk": c.value}
+
+
+def swiftcl_workspace_points(plan, limit=-1):
+    a, g = ctypes.c_int32(), ctypes.c_int32()
+    _check(load().swiftcl_workspace_points(plan, limit, ctypes.byref(a), ctypes.byref(g)))
+    return {"adjoint": a.value, "growth": g.value}
 
 
 def swiftcl_get_launch(plan):

@@ -156,6 +156,7 @@ struct swiftcl_plan_s {
   plan_dev d{};
   std::vector<double> ell_host;
   size_t real_size = 4;  // sizeof(real) on the FFT path
+  int wchunk_built = 0, kc_built = 0;  // the chunks that the workspace holds (swiftcl_workspace_points limits them)
   // inputs whose assembly and FFTLog coefficients the last forward launch left in the workspace
   bool fwd_valid = false;
   swiftcl_inputs fwd_in{};

@@ -696,6 +696,8 @@ extern "C" swiftcl_status swiftcl_plan(const swiftcl_plan_desc* d, void* stream,
       free_workspace(p->d);
     }
     if (!ok) { free_plan(p); return SWIFTCL_E_NOMEM; }
+    p->wchunk_built = p->d.wchunk;
+    p->kc_built = p->d.kc_chunk;
   }
 
   // --- uploads (host tables converted to the FFT precision) ---
@@ -1264,6 +1266,17 @@ extern "C" swiftcl_status swiftcl_plan_info(swiftcl_plan_t p, int32_t* fused, in
   if (fused) *fused = p->d.fused;
   if (adjoint) *adjoint = p->d.adjoint;
   if (point_chunk) *point_chunk = p->d.vbuf ? p->d.vchunk : 0;
+  return SWIFTCL_OK;
+}
+
+extern "C" swiftcl_status swiftcl_workspace_points(swiftcl_plan_t p, int32_t limit, int32_t* adjoint, int32_t* growth) {
+  if (!p) { set_error("plan is NULL"); return SWIFTCL_E_INVALID; }
+  if (limit >= 0) {
+    p->d.wchunk = limit ? std::min(limit, p->wchunk_built) : p->wchunk_built;
+    p->d.kc_chunk = limit ? std::min(limit, p->kc_built) : p->kc_built;
+  }
+  if (adjoint) *adjoint = p->d.adjoint == 2 && p->d.vbuf && !bwd_in_lds(p->d) ? p->d.wchunk : 0;
+  if (growth) *growth = p->d.kc_chunk;
   return SWIFTCL_OK;
 }
 

@@ -378,8 +378,14 @@ class Plan:
 
     @property
     def vchunk(self):
-        """Points per chunk of the workspace paths (0 without a workspace)."""
+        """Points per chunk of cl_kgrowth_nodes and the growth gradients; the multipole chunks of the
+        workspace adjoint are sized for it (0 without a workspace)."""
         return bd.swiftcl_plan_info(self.handle)["point_chunk"]
+
+    def workspace_points(self, limit=None):
+        """Points that the workspace adjoint and cl_kgrowth run at once (swiftcl_workspace_points).  limit: at
+        most that many in later calls; 0: as many as the workspace holds."""
+        return bd.swiftcl_workspace_points(self.handle, -1 if limit is None else int(limit))
 
     def device_flags(self):
         return bd.swiftcl_device_flags(self.handle, self._stream())

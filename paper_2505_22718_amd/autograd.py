@@ -82,12 +82,12 @@ class ClKgrowthFunction(torch.autograd.Function):
         t = dict(inputs)
         t.update(pk=pk.detach().contiguous(), bias=bias.detach().contiguous())
         D = D_kz.detach().contiguous()
-        # dL/db is formed from C, so C then comes from the windows that the adjoint sums
-        C = plan.cl_kgrowth_nodes(t, D) if ctx.needs_input_grad[4] else plan.cl_kgrowth(t, D)
+        C = plan.cl_kgrowth(t, D)
         ctx.plan = plan
         ctx.t = t
         ctx.D = D
-        ctx.save_for_backward(pk, bias, C)
+        # torch checks at backward time that none of these was modified in place since
+        ctx.save_for_backward(D_kz, pk, bias)
         return C
 
     @staticmethod
@@ -97,8 +97,9 @@ class ClKgrowthFunction(torch.autograd.Function):
         want = [name for name, need in zip(("pk", "bias"), ctx.needs_input_grad[3:]) if need]
         if not want:
             return None, None, None, None, None
-        _, _, C = ctx.saved_tensors
-        g = ctx.plan.kgrowth_backward(ctx.t, ctx.D, C, dC.to(ctx.plan.out_dtype).contiguous(), want=tuple(want))
+        ctx.saved_tensors  # raises if an input was modified in place after the forward call
+        # (dL/db is formed from C: from that of the windows which the adjoint sums)
+        g = ctx.plan.kgrowth_nodes_backward(ctx.t, ctx.D, dC.to(ctx.plan.out_dtype).contiguous(), want=tuple(want))
         return None, None, None, g.get("pk"), g.get("bias")
 
 

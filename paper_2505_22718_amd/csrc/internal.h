@@ -192,8 +192,9 @@ hipError_t launch_kgrowth(const plan_dev& p, const swiftcl_inputs* in, const dou
 hipError_t launch_kgrowth_conv(const plan_dev& p, const swiftcl_inputs* in, const double* D_kz, void* C, hipStream_t s);
 void kgrowth_conv_sizes(plan_dev& p);          // sets kc_ns, kc_sp and kc_sk
 size_t kgrowth_conv_bytes(const plan_dev& p);  // then its workspace per point, but for vbuf
+// Cn (optional): C by the node coefficients, formed here and taken for dL/db in place of C
 hipError_t launch_kgrowth_backward(const plan_dev& p, const swiftcl_inputs* in, const double* D_kz, const void* C,
-                                   const void* dC, double* dpk, double* dbias, hipStream_t s);
+                                   void* Cn, const void* dC, double* dpk, double* dbias, hipStream_t s);
 hipError_t launch_bwd_gv(const plan_dev& p, const swiftcl_inputs* in, const void* dC, int b0, int nbp, hipStream_t s);
 hipError_t launch_bwd_dpk(const plan_dev& p, const swiftcl_inputs* in, double* dpk, hipStream_t s);
 size_t kgrowth_fft_lds(int M, int n_zg);  // dynamic LDS of the node-coefficient kernel

@@ -536,72 +536,72 @@ size_t kg_fft_lds(int n_zg) {
   return sizeof(float2) * 2 * (size_t)M + sizeof(float) * 2 * M + (fft > spl ? fft : spl);
 }
 
+// Node coefficients of points [b0, b0 + nbp) and their spline moments (kg_c, kg_m), the multipole slots by band
+template <int M>
+hipError_t launch_kg_nodes(const plan_dev& p, const swiftcl_inputs* in, const double* D_kz, int b0, int nbp,
+                           hipStream_t s) {
+  const double h = (double)(p.n_k - 1) * p.delta / (double)(p.n_interp - 1);
+  hipLaunchKernelGGL(k_kg_slots, dim3(nbp), dim3(SWIFTCL_WAVE), 0, s, p, *in, b0, nbp);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_kg_fft<M>, dim3((unsigned)((size_t)nbp * p.n_interp)), dim3(256), kg_fft_lds<M>(p.n_zg), s, p,
+                     *in, D_kz, b0, nbp);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  hipLaunchKernelGGL(k_kg_cspline, dim3((unsigned)((size_t)nbp * p.max_tracers * p.n_bands), (M + 255) / 256), dim3(256),
+                     0, s, p, *in, b0, nbp, (float)(6.0 / (h * h)));
+  return hipGetLastError();
+}
+
+// Windows of these points into the workspace: sqrt(s) W for the projection, or (w_only, FP32) W
+hipError_t launch_kg_windows(const plan_dev& p, const swiftcl_inputs* in, int b0, int nbp, bool w_only, hipStream_t s) {
+  const int NJ = (p.n_k + KG_TILE - 1) / KG_TILE;
+  const size_t groups = ((size_t)nbp * p.max_tracers + SWIFTCL_NXCD - 1) / SWIFTCL_NXCD;
+  const dim3 gw((unsigned)(groups * p.kg_ntile * NJ * SWIFTCL_NXCD));
+  auto kernel = p.kg_stage ? k_kg_windows<false, false, true> : k_kg_windows<false>;
+  if (w_only) kernel = p.kg_stage ? k_kg_windows<false, true, true> : k_kg_windows<false, true>;
+  else if (p.precision == SWIFTCL_SPLIT_BF16) kernel = p.kg_stage ? k_kg_windows<true, false, true> : k_kg_windows<true>;
+  hipLaunchKernelGGL(kernel, gw, dim3(256), 0, s, p, *in, b0, nbp);
+  return hipGetLastError();
+}
+
 template <int M>
 hipError_t launch_kg_t(const plan_dev& p, const swiftcl_inputs* in, const double* D_kz, void* C, hipStream_t s) {
-  const int T = p.max_tracers, nb = p.n_bands, A = p.n_interp;
-  const double h = (double)(p.n_k - 1) * p.delta / (double)(A - 1);
-  const float s6 = (float)(6.0 / (h * h));
-  const int NJ = (p.n_k + KG_TILE - 1) / KG_TILE;
-  const bool split = p.precision == SWIFTCL_SPLIT_BF16;
   for (int b0 = 0; b0 < in->batch; b0 += p.vchunk) {
     const int nbp = in->batch - b0 < p.vchunk ? in->batch - b0 : p.vchunk;
-    hipLaunchKernelGGL(k_kg_slots, dim3(nbp), dim3(SWIFTCL_WAVE), 0, s, p, *in, b0, nbp);
-    hipError_t e = hipGetLastError();
+    hipError_t e = launch_kg_nodes<M>(p, in, D_kz, b0, nbp, s);
+    if (e == hipSuccess) e = launch_kg_windows(p, in, b0, nbp, false, s);
+    if (e == hipSuccess) e = launch_contract(p, in, C, b0, nbp, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_kg_fft<M>, dim3((unsigned)((size_t)nbp * A)), dim3(256), kg_fft_lds<M>(p.n_zg), s, p, *in,
-                       D_kz, b0, nbp);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_kg_cspline, dim3((unsigned)((size_t)nbp * T * nb), (M + 255) / 256), dim3(256), 0, s, p,
-                       *in, b0, nbp, s6);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    const size_t pairs = (size_t)nbp * T;
-    const size_t groups = (pairs + SWIFTCL_NXCD - 1) / SWIFTCL_NXCD;
-    const dim3 gw((unsigned)(groups * p.kg_ntile * NJ * SWIFTCL_NXCD));
-    if (p.kg_stage) {
-      if (split) hipLaunchKernelGGL((k_kg_windows<true, false, true>), gw, dim3(256), 0, s, p, *in, b0, nbp);
-      else hipLaunchKernelGGL((k_kg_windows<false, false, true>), gw, dim3(256), 0, s, p, *in, b0, nbp);
-    } else {
-      if (split) hipLaunchKernelGGL(k_kg_windows<true>, gw, dim3(256), 0, s, p, *in, b0, nbp);
-      else hipLaunchKernelGGL(k_kg_windows<false>, gw, dim3(256), 0, s, p, *in, b0, nbp);
-    }
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    if ((e = launch_contract(p, in, C, b0, nbp, s)) != hipSuccess) return e;
   }
   return hipSuccess;
 }
 
-// Adjoint (dL/dP, dL/db): the windows recomputed as W rows, then Y = G W with the dP partials
-// (the workspace adjoint's kernels), their reduction, and dL/db from the forward output C.
+// Adjoint (dL/dP, dL/db): the windows recomputed as W rows, then Y = G W with the dP partials (the workspace
+// adjoint's kernels), their reduction, and dL/db from C: the forward output, or (Cn) the C of the same node
+// coefficients, formed here.
 template <int M>
-hipError_t launch_kg_bwd_t(const plan_dev& p, const swiftcl_inputs* in, const double* D_kz, const void* C,
+hipError_t launch_kg_bwd_t(const plan_dev& p, const swiftcl_inputs* in, const double* D_kz, const void* C, void* Cn,
                            const void* dC, double* dpk, double* dbias, hipStream_t s) {
-  const int T = p.max_tracers, nb = p.n_bands, A = p.n_interp;
-  const double h = (double)(p.n_k - 1) * p.delta / (double)(A - 1);
-  const float s6 = (float)(6.0 / (h * h));
-  const int NJ = (p.n_k + KG_TILE - 1) / KG_TILE;
-  hipError_t e;
-  if (dpk) {
+  const int T = p.max_tracers;
+  hipError_t e = hipSuccess;
+  if (dpk || Cn) {
     for (int b0 = 0; b0 < in->batch; b0 += p.vchunk) {
       const int nbp = in->batch - b0 < p.vchunk ? in->batch - b0 : p.vchunk;
-      hipLaunchKernelGGL(k_kg_slots, dim3(nbp), dim3(SWIFTCL_WAVE), 0, s, p, *in, b0, nbp);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-      hipLaunchKernelGGL(k_kg_fft<M>, dim3((unsigned)((size_t)nbp * A)), dim3(256), kg_fft_lds<M>(p.n_zg), s, p,
-                         *in, D_kz, b0, nbp);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-      hipLaunchKernelGGL(k_kg_cspline, dim3((unsigned)((size_t)nbp * T * nb), (M + 255) / 256), dim3(256), 0, s, p,
-                         *in, b0, nbp, s6);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
+      if ((e = launch_kg_nodes<M>(p, in, D_kz, b0, nbp, s)) != hipSuccess) return e;
+      if (Cn) {
+        e = launch_kg_windows(p, in, b0, nbp, false, s);
+        if (e == hipSuccess) e = launch_contract(p, in, Cn, b0, nbp, s);
+        if (e != hipSuccess) return e;
+      }
+      if (!dpk) continue;
       hipLaunchKernelGGL(k_kg_zero, dim3((unsigned)((size_t)nbp * p.max_ell)), dim3(256), 0, s, p, *in, b0, nbp);
       if ((e = hipGetLastError()) != hipSuccess) return e;
-      const size_t groups = ((size_t)nbp * T + SWIFTCL_NXCD - 1) / SWIFTCL_NXCD;
-      const dim3 gw((unsigned)(groups * p.kg_ntile * NJ * SWIFTCL_NXCD));
-      if (p.kg_stage) hipLaunchKernelGGL((k_kg_windows<false, true, true>), gw, dim3(256), 0, s, p, *in, b0, nbp);
-      else hipLaunchKernelGGL((k_kg_windows<false, true>), gw, dim3(256), 0, s, p, *in, b0, nbp);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
+      if ((e = launch_kg_windows(p, in, b0, nbp, true, s)) != hipSuccess) return e;
       if ((e = launch_bwd_gv(p, in, dC, b0, nbp, s)) != hipSuccess) return e;
     }
-    if ((e = launch_bwd_dpk(p, in, dpk, s)) != hipSuccess) return e;
+    if (dpk && (e = launch_bwd_dpk(p, in, dpk, s)) != hipSuccess) return e;
   }
+  if (Cn) C = Cn;
   if (dbias) {
     hipLaunchKernelGGL(k_kg_dbias, dim3((unsigned)((size_t)in->batch * T)), dim3(64), 0, s, p, *in,
                        (const float*)C, (const float*)dC, dbias);
@@ -613,12 +613,12 @@ hipError_t launch_kg_bwd_t(const plan_dev& p, const swiftcl_inputs* in, const do
 }  // namespace
 
 hipError_t launch_kgrowth_backward(const plan_dev& p, const swiftcl_inputs* in, const double* D_kz, const void* C,
-                                   const void* dC, double* dpk, double* dbias, hipStream_t s) {
+                                   void* Cn, const void* dC, double* dpk, double* dbias, hipStream_t s) {
   switch (p.M) {
-    case 128: return launch_kg_bwd_t<128>(p, in, D_kz, C, dC, dpk, dbias, s);
-    case 256: return launch_kg_bwd_t<256>(p, in, D_kz, C, dC, dpk, dbias, s);
-    case 512: return launch_kg_bwd_t<512>(p, in, D_kz, C, dC, dpk, dbias, s);
-    case 1024: return launch_kg_bwd_t<1024>(p, in, D_kz, C, dC, dpk, dbias, s);
+    case 128: return launch_kg_bwd_t<128>(p, in, D_kz, C, Cn, dC, dpk, dbias, s);
+    case 256: return launch_kg_bwd_t<256>(p, in, D_kz, C, Cn, dC, dpk, dbias, s);
+    case 512: return launch_kg_bwd_t<512>(p, in, D_kz, C, Cn, dC, dpk, dbias, s);
+    case 1024: return launch_kg_bwd_t<1024>(p, in, D_kz, C, Cn, dC, dpk, dbias, s);
   }
   return hipErrorInvalidValue;
 }

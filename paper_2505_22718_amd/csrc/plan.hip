@@ -916,13 +916,12 @@ extern "C" swiftcl_status swiftcl_cl_kgrowth_nodes(swiftcl_plan_t p, const swift
   return run_kgrowth(p, in, D_kz, C, stream, true);
 }
 
-extern "C" swiftcl_status swiftcl_cl_kgrowth_backward(swiftcl_plan_t p, const swiftcl_inputs* in, const double* D_kz,
-                                                      const void* C, const void* dC, double* dpk, double* dbias,
-                                                      void* stream) {
+static swiftcl_status run_kgrowth_backward(swiftcl_plan_t p, const swiftcl_inputs* in, const double* D_kz, const void* C,
+                                           void* Cn, const void* dC, double* dpk, double* dbias, void* stream) {
   if (!p) { set_error("plan is NULL"); return SWIFTCL_E_INVALID; }
   if (!in) { set_error("inputs is NULL"); return SWIFTCL_E_INVALID; }
   if (!D_kz || !dC) { set_error("D_kz or dC is NULL"); return SWIFTCL_E_INVALID; }
-  if (dbias && !C) { set_error("dbias needs C, the forward output"); return SWIFTCL_E_INVALID; }
+  if (dbias && !C && !Cn) { set_error("dbias needs C, the forward output"); return SWIFTCL_E_INVALID; }
   if (p->d.n_interp < 2) {
     set_error("the plan has no interpolation nodes in k (n_interp = 0)");
     return SWIFTCL_E_INVALID;
@@ -944,12 +943,24 @@ extern "C" swiftcl_status swiftcl_cl_kgrowth_backward(swiftcl_plan_t p, const sw
   hipStream_t s = (hipStream_t)stream;
   p->fwd_valid = false;
   hipError_t e = hipSuccess;
-  if (dpk) {
+  if (dpk || Cn) {
     e = launch_assemble(p->d, &in1, s);
     if (e == hipSuccess) e = launch_sqrt_s(p->d, &in1, s);
   }
-  if (e == hipSuccess) e = launch_kgrowth_backward(p->d, &in1, D_kz, C, dC, dpk, dbias, s);
+  if (e == hipSuccess) e = launch_kgrowth_backward(p->d, &in1, D_kz, C, Cn, dC, dpk, dbias, s);
   return hip_check(e, "scale-dependent growth backward launch");
+}
+
+extern "C" swiftcl_status swiftcl_cl_kgrowth_backward(swiftcl_plan_t p, const swiftcl_inputs* in, const double* D_kz,
+                                                      const void* C, const void* dC, double* dpk, double* dbias,
+                                                      void* stream) {
+  return run_kgrowth_backward(p, in, D_kz, C, nullptr, dC, dpk, dbias, stream);
+}
+
+extern "C" swiftcl_status swiftcl_cl_kgrowth_nodes_backward(swiftcl_plan_t p, const swiftcl_inputs* in,
+                                                            const double* D_kz, void* C, const void* dC, double* dpk,
+                                                            double* dbias, void* stream) {
+  return run_kgrowth_backward(p, in, D_kz, nullptr, dbias ? C : nullptr, dC, dpk, dbias, stream);
 }
 
 extern "C" swiftcl_status swiftcl_cl_limber(swiftcl_plan_t p, const swiftcl_inputs* in, void* C, void* stream) {

@@ -251,20 +251,29 @@ class Plan:
 
     def kgrowth_backward(self, t, D_kz, C, dC, want=("pk", "bias")):
         """Gradients of sum(dC * C_kgrowth) with respect to pk and bias (swiftcl_cl_kgrowth_backward);
-        C is cl_kgrowth's output for the same inputs."""
+        C is cl_kgrowth's (or cl_kgrowth_nodes') output for the same inputs."""
+        return self._kgrowth_backward(bd.swiftcl_cl_kgrowth_backward, t, D_kz, C.contiguous(), dC, want)
+
+    def kgrowth_nodes_backward(self, t, D_kz, dC, want=("pk", "bias")):
+        """kgrowth_backward without the forward's output: the bias gradient from the C of the adjoint's own
+        windows (swiftcl_cl_kgrowth_nodes_backward)."""
+        return self._kgrowth_backward(bd.swiftcl_cl_kgrowth_nodes_backward, t, D_kz, None, dC, want)
+
+    def _kgrowth_backward(self, call, t, D_kz, C, dC, want):
         s = self.inputs_struct(t)
         B = s.batch
         check_tensor("D_kz", D_kz, (B, self.n_interp, len(self.z_geom)), torch.float64, self.device)
-        C = self._cl_buffer("C", C.contiguous(), B)
+        if C is not None or "bias" in want:
+            C = self._cl_buffer("C", C, B)
         dC = self._cl_buffer("dC", dC.contiguous(), B)
         bad = set(want) - {"pk", "bias"}
         if bad:
             raise ValueError(f"the scale-dependent growth adjoint gives pk and bias gradients, not {sorted(bad)}")
         outs = self._grad_outputs(B, want)
         self._new_state()
-        bd.swiftcl_cl_kgrowth_backward(self.handle, s, D_kz.data_ptr(), C.data_ptr(), dC.data_ptr(),
-                                       outs["pk"].data_ptr() if outs["pk"] is not None else 0,
-                                       outs["bias"].data_ptr() if outs["bias"] is not None else 0, self._stream())
+        call(self.handle, s, D_kz.data_ptr(), C.data_ptr() if C is not None else 0, dC.data_ptr(),
+             outs["pk"].data_ptr() if outs["pk"] is not None else 0,
+             outs["bias"].data_ptr() if outs["bias"] is not None else 0, self._stream())
         return {k: v for k, v in outs.items() if v is not None}
 
     def cl_limber(self, t, out=None):

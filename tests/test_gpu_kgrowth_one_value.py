@@ -1,0 +1,63 @@
+"""C of scale-dependent growth is one value, whatever gradients are asked for: autograd's C equals the plan's bit
+for bit, and the gradients are those of the node coefficients (dL/db from their C) in chunks of any size."""
+import numpy as np
+import pytest
+import torch
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dev():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch.device("cuda:0")
+
+
+def _setup(dev, precision="fp32"):
+    from paper_2505_22718_amd.plan import Plan, device_inputs
+    wl = synth.make_workload("cfg1")
+    synth.scale_dependent_growth(wl, 24, f_nu=0.3)
+    wl["ell_idx"] = np.ascontiguousarray(wl["ell_idx"][:, ::9])
+    wl["n_ell"] = np.array([wl["ell_idx"].shape[1]], np.int32)
+    for n in ("n_tracers", "kind", "n_ell", "ell_idx", "chi_z", "D_z", "omega_m", "nz", "bias", "pk", "D_kz"):
+        wl[n] = np.ascontiguousarray(np.repeat(wl[n], 3, 0))
+    wl["bias"] = wl["bias"] * (1.0 + 0.1 * np.arange(3))[:, None]
+    wl["batch"] = 3
+    p = Plan.for_workload(wl, precision=precision, n_interp=24)
+    return p, device_inputs(wl, dev), torch.as_tensor(wl["D_kz"], dtype=torch.float64, device=dev)
+
+
+@pytest.mark.parametrize("precision", ["fp32", "split_bf16"])
+@pytest.mark.parametrize("grads", [("pk", "bias"), ("pk",), ("bias",), ()])
+def test_one_value(dev, grads, precision):
+    from paper_2505_22718_amd import autograd
+    p, t, D = _setup(dev, precision)
+    ref = p.cl_kgrowth(t, D)
+    leaves = {n: t[n].clone().requires_grad_(n in grads) for n in ("pk", "bias")}
+    with torch.set_grad_enabled(bool(grads)):
+        C = autograd.cl_kgrowth(p, t, D, leaves["pk"], leaves["bias"])
+    assert bool(torch.equal(C.detach(), ref))
+    if not grads:
+        return
+    dC = torch.randn(C.shape, generator=torch.Generator().manual_seed(9)).to(dev)
+    (C * dC).sum().backward()
+    g = p.kgrowth_backward(t, D, p.cl_kgrowth_nodes(t, D), dC)
+    assert p.device_flags() == 0
+    for n in ("pk", "bias"):
+        if n in grads:
+            assert bool(torch.equal(leaves[n].grad, g[n])), n
+        else:
+            assert leaves[n].grad is None
+
+
+def test_inputs_changed_before_backward_are_refused(dev):
+    from paper_2505_22718_amd import autograd
+    p, t, D = _setup(dev)
+    bias = t["bias"].clone().requires_grad_(True)
+    C = autograd.cl_kgrowth(p, t, D, t["pk"], bias)
+    D.mul_(1.1)
+    with pytest.raises(RuntimeError, match="modified by an inplace operation"):
+        C.sum().backward()

@@ -707,12 +707,11 @@ __global__ __launch_bounds__(1024) void k_bwd_wy(plan_dev P, swiftcl_inputs in, 
   using S = wy_shape<M, NT>;
   typedef float R;
   constexpr int RL = S::RL, N = 2 * M, FL = fft_lds_size(M, sizeof(R));
-  constexpr bool TW = unfused_tw(M);
   constexpr int NTW = (S::SW / 16 + 15) / 16;  // 16-wide k tiles per wavefront and slab
   constexpr int NST = 4 * NT;                  // steps of 4 tracers
   float* Gp = (float*)smem;                           // [NT][NST][64]: what lane l feeds, G[16 it + l % 16][4 st + l / 16]
-  C2<R>* stw_l = (C2<R>*)(Gp + NT * NST * 64);        // [N]
-  C2<R>* fbuf = stw_l + (TW ? N : 0);                 // [16][FL] transform scratch, then
+  C2<R>* stw = (C2<R>*)(Gp + NT * NST * 64);          // [N]
+  C2<R>* fbuf = stw + N;                              // [16][FL] transform scratch, then
   float* slab = (float*)fbuf;                         // [2][16 NT][SP]
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid / SWIFTCL_WAVE), lane0 = tid % SWIFTCL_WAVE;
@@ -721,9 +720,7 @@ __global__ __launch_bounds__(1024) void k_bwd_wy(plan_dev P, swiftcl_inputs in, 
   xcd_item(blockIdx.x, nbp, nlc, &bl, &c);
   if (bl >= nbp) return;
   const int b = b0 + bl;
-  const C2<R>* stw = TW ? stw_l : (const C2<R>*)P.tw;
-  if (TW)
-    for (int i = tid; i < N; i += 1024) stw_l[i] = ((const C2<R>*)P.tw)[i];
+  for (int i = tid; i < N; i += 1024) stw[i] = ((const C2<R>*)P.tw)[i];
   const int Tb = clampb(in.n_tracers[b], 0, T);
   const int Lb = clampb(in.n_ell[b], 0, Lm);
   const int l0 = (int)(((long)c * Lb) / nlc), l1 = (int)(((long)(c + 1) * Lb) / nlc);
@@ -845,7 +842,7 @@ static hipError_t launch_bwd_wy(const plan_dev& p, const swiftcl_inputs* in, con
   const dim3 grid(xcd_blocks(nbp, p.bwd_nlc));
 #define SWIFTCL_WY(NT, EX)                                                                                        \
   hipLaunchKernelGGL((k_bwd_wy<M, NT, EX>), grid, dim3(1024),                                                     \
-                     (wy_shape<M, NT>::bytes(unfused_tw(M)) + (size_t)NT * NT * 4 * 64 * sizeof(float)), s, p, *in, \
+                     (wy_shape<M, NT>::bytes() + (size_t)NT * NT * 4 * 64 * sizeof(float)), s, p, *in, \
                      (const float*)dC, b0, nbp, p.bwd_nlc)
 #define SWIFTCL_WY2(EX)                        \
   do {                                         \
@@ -870,12 +867,12 @@ static hipError_t launch_bwd_wy(const plan_dev& p, const swiftcl_inputs* in, con
 // Bound by the FP32 issue of the transforms; the row of the next multipole is loaded during this one's
 // transform (1.82 -> 1.30 ms for 64 points of 30 tracers, n_chi = 2048; three wavefronts per SIMD, 51 KB
 // of LDS).
-template <int M, bool TW_LDS>
+template <int M>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_bwd_adj(plan_dev P, swiftcl_inputs in, int b0, int nbp, int nlc) {
   constexpr int RL = M / SWIFTCL_WAVE;
   constexpr int N = 2 * M;
   __shared__ C2<float> lds[4][fft_lds_size(M, sizeof(float))];
-  __shared__ C2<float> stw_s[TW_LDS ? N : 1];
+  __shared__ C2<float> stw[N];
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid / SWIFTCL_WAVE), lane = tid % SWIFTCL_WAVE;
   const int T = P.max_tracers, Lm = P.max_ell, nk = P.n_k, nb = P.n_bands;
@@ -885,11 +882,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
   const int c = rest % nlc;
   const int bl = rest / nlc;
   if (bl >= nbp) return;
-  if constexpr (TW_LDS) {
-    for (int i = tid; i < N; i += 256) stw_s[i] = ((const C2<float>*)P.tw)[i];
-    __syncthreads();
-  }
-  const C2<float>* stw = TW_LDS ? (const C2<float>*)stw_s : (const C2<float>*)P.tw;
+  for (int i = tid; i < N; i += 256) stw[i] = ((const C2<float>*)P.tw)[i];
+  __syncthreads();
   const int b = b0 + bl;
   const int t = 4 * g + wave;
   const int Tb = clampb(in.n_tracers[b], 0, T);
@@ -1676,7 +1670,7 @@ static hipError_t launch_bwd_ws(const plan_dev& p, const swiftcl_inputs* in, con
   for (int b0 = 0; !rows && b0 < in->batch; b0 += most) {
     const int nbp = in->batch - b0 < most ? in->batch - b0 : most;
     if ((e = launch_bwd_wy<M>(p, in, dC, b0, nbp, s)) != hipSuccess) return e;
-    hipLaunchKernelGGL((k_bwd_adj<M, (M <= 1024)>), dim3((unsigned)((size_t)nbp * nlc * ng)), dim3(256), 0, s, p,
+    hipLaunchKernelGGL(k_bwd_adj<M>, dim3((unsigned)((size_t)nbp * nlc * ng)), dim3(256), 0, s, p,
                        *in, b0, nbp, nlc);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }

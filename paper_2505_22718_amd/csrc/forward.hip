@@ -507,7 +507,6 @@ template <int M> struct wcl_shape<double, M> {
 
 int windows_nw(int precision) { return precision == SWIFTCL_FP64 ? 2 : 16; }
 bool windows_tw_lds(int precision, int M) { return precision != SWIFTCL_FP64 && M <= 512; }
-bool unfused_tw_lds(int M) { return unfused_tw(M); }
 
 // ---------------------------------------------------------------------------------------------
 // Projection of plans that k_windows_cl does not hold (17..32 tracers, n_chi = 2048, RSD and
@@ -522,7 +521,7 @@ bool unfused_tw_lds(int M) { return unfused_tw(M); }
 // ---------------------------------------------------------------------------------------------
 template <int M, int NT> using wp_shape = slab_shape<M, NT, 4, NT == 2 ? 3 : 1>;  // 16-byte reads on distinct banks
 
-template <int M, int NT, bool TW_LDS, bool SPLIT, int EXTRA>
+template <int M, int NT, bool SPLIT, int EXTRA>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(M <= 512 ? 8 : 4))) void k_windows_p(
     plan_dev P, swiftcl_inputs in, float* __restrict__ Cout, int b0, int nbp) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -530,8 +529,8 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(M <= 512 ?
   constexpr int TILES = NT == 2 ? 3 : 1;
   typedef float R;
   constexpr int RL = S::RL, N = 2 * M, FL = fft_lds_size(M, sizeof(R));
-  C2<R>* stw_l = (C2<R>*)smem;                                    // [N] (TW_LDS)
-  C2<R>* fbuf = stw_l + (TW_LDS ? N : 0);                         // [16][FL] transform scratch, then
+  C2<R>* stw = (C2<R>*)smem;                                      // [N]
+  C2<R>* fbuf = stw + N;                                          // [16][FL] transform scratch, then
   float* slab = (float*)fbuf;                                     // [2][16 NT][SP], then [16][TILES][256]
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / SWIFTCL_WAVE), lane = threadIdx.x % SWIFTCL_WAVE;
   const int T = P.max_tracers, Lm = P.max_ell, nk = P.n_k, nb = P.n_bands;
@@ -552,11 +551,8 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(M <= 512 ?
     ei = 0;
   }
   const int band = P.ell_band[ei];
-  const C2<R>* stw = TW_LDS ? stw_l : (const C2<R>*)P.tw;
-  if constexpr (TW_LDS) {
-    for (int i = threadIdx.x; i < N; i += 1024) stw_l[i] = ((const C2<R>*)P.tw)[i];
-    __syncthreads();
-  }
+  for (int i = threadIdx.x; i < N; i += 1024) stw[i] = ((const C2<R>*)P.tw)[i];
+  __syncthreads();
   C2<R> x[NT][RL];
 #pragma unroll
   for (int i = 0; i < NT; ++i) {
@@ -793,14 +789,13 @@ hipError_t launch_sqrt_s(const plan_dev& p, const swiftcl_inputs* in, hipStream_
 
 template <int M>
 static hipError_t launch_unfused(const plan_dev& p, const swiftcl_inputs* in, void* C, hipStream_t s) {
-  constexpr bool TW = unfused_tw(M);
   const bool split = p.precision == SWIFTCL_SPLIT_BF16;
   const int most = points_per_launch(p.max_ell, 1024);
   for (int b0 = 0; b0 < in->batch; b0 += most) {
     const int nbp = in->batch - b0 < most ? in->batch - b0 : most;
     const dim3 grid(xcd_blocks(nbp, p.max_ell));
 #define SWIFTCL_WP(NT, SP, EX)                                                                                    \
-  hipLaunchKernelGGL((k_windows_p<M, NT, TW, SP, EX>), grid, dim3(1024), (wp_shape<M, NT>::bytes(TW)), s, p, *in, \
+  hipLaunchKernelGGL((k_windows_p<M, NT, SP, EX>), grid, dim3(1024), (wp_shape<M, NT>::bytes()), s, p, *in, \
                      (float*)C, b0, nbp)
 #define SWIFTCL_WP2(SP, EX)                \
   do {                                     \

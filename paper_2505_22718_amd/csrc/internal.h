@@ -171,7 +171,6 @@ swiftcl_status noalloc_setup(int device);
 inline bool bwd_in_lds(const plan_dev& p) { return p.max_tracers <= 16 && p.M <= 512; }
 size_t bwd_windows_lds(const plan_dev& p);  // dynamic LDS of the adjoint windows kernel
 size_t windows_cl_lds(int M, int NW, bool tw_lds, bool do_cl, size_t rs, int n_k);
-bool unfused_tw_lds(int M);
 size_t geometry_lds_bytes(const plan_dev& p);
 int windows_nw(int precision);
 bool windows_tw_lds(int precision, int M);

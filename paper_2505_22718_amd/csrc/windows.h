@@ -4,23 +4,21 @@
 #include "common.h"
 #include "internal.h"
 
-// the unfused FP32 kernels stage the twiddles in LDS up to n_chi = 2048
-constexpr bool unfused_tw(int M) { return M <= 1024; }
-
 // Shape of a kernel of 16 wavefronts that keeps the rows of NT tracers per wavefront in registers and passes
 // them through LDS in slabs of k, double-buffered in the space of the transforms' scratch.  PAD: floats after a
-// slab row; TILES: 16 x 16 result tiles summed over the wavefronts at the end (0: none).
+// slab row; TILES: 16 x 16 result tiles summed over the wavefronts at the end (0: none).  bytes: with the
+// twiddles before it.
 template <int M, int NT, int PAD, int TILES> struct slab_shape {
   static constexpr int RL = M / SWIFTCL_WAVE;
   static constexpr int SE = NT == 2 ? (RL >= 4 ? RL / 4 : 1) : RL / 2;  // register pairs per slab
   static constexpr int NS = RL / SE;                                    // slabs
   static constexpr int SW = 2 * SWIFTCL_WAVE * SE;                      // k nodes per slab
   static constexpr int SP = SW + PAD;                                   // row stride
-  static constexpr size_t bytes(bool tw) {
+  static constexpr size_t bytes() {
     size_t n = (size_t)16 * fft_lds_size(M, 4) * 8;
     if ((size_t)2 * 16 * NT * SP * 4 > n) n = (size_t)2 * 16 * NT * SP * 4;
     if ((size_t)16 * TILES * 1024 > n) n = (size_t)16 * TILES * 1024;
-    return n + (tw ? (size_t)2 * M * 8 : 0);
+    return n + (size_t)2 * M * 8;
   }
 };
 

@@ -51,11 +51,12 @@ def bwd_kernel_flops(T, L, B, N, n_k):
 
 
 KERNEL_SOURCES = ["paper_2505_22718_amd/csrc/backward.hip", "paper_2505_22718_amd/csrc/common.h",
-                  "paper_2505_22718_amd/csrc/internal.h"]
+                  "paper_2505_22718_amd/csrc/internal.h", "paper_2505_22718_amd/csrc/xcd_map.h"]
 TRAFFIC_RECORD = os.path.join(ROOT, "profiles", "pmc_k_bwd_windows_cfg1_batch256.md")
 # the same for the forward windows + projection kernel
 FWD_KERNEL_SOURCES = ["paper_2505_22718_amd/csrc/forward.hip", "paper_2505_22718_amd/csrc/common.h",
-                      "paper_2505_22718_amd/csrc/internal.h", "paper_2505_22718_amd/csrc/sched_layout.h"]
+                      "paper_2505_22718_amd/csrc/internal.h", "paper_2505_22718_amd/csrc/sched_layout.h",
+                      "paper_2505_22718_amd/csrc/xcd_map.h"]
 FWD_TRAFFIC_RECORD = os.path.join(ROOT, "profiles", "pmc_k_windows_cl_cfg1_batch256.md")
 PEAK_HBM_GBPS = 8000.0
 PEAK_FP32_MFMA_TFLOPS = 157.3

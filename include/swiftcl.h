@@ -96,9 +96,9 @@ typedef struct {
   int32_t rsd;          /* 1: redshift-space distortions of the clustering tracers (eq. RSD),
                            -int dchi f(z) n dz/dchi D j_l''(k chi) added to their windows, with
                            f = dln D/dln a from the D(z) spline; 0: none.  FP32 and split plans;
-                           the projection runs through the workspace; swiftcl_windows,
-                           swiftcl_cl_backward, swiftcl_cl_kgrowth and swiftcl_cl_limber refuse
-                           such plans                                                              */
+                           swiftcl_cl_backward gives dL/dP and dL/db of such plans (dnz and dD must
+                           be NULL); swiftcl_windows, swiftcl_cl_kgrowth, swiftcl_cl_limber and
+                           swiftcl_cl_noalloc refuse them                                          */
   int32_t magnification; /* 1: the plan can carry magnification bias of the clustering tracers
                            (eq. magnification bias; inputs `mag`), with the same restrictions as
                            rsd; 0: none                                                            */
@@ -276,13 +276,11 @@ swiftcl_status swiftcl_cl_backward_timed(swiftcl_plan_t plan, const swiftcl_inpu
                                          void* stream, float* stage_ms);
 
 /* Angular power spectra with scale-dependent growth D(k, z) (Sec. 3.2: P(k, chi, chi') =
- * P(k, z_fid) D(k, z(chi)) D(k, z(chi')), FFTLog coefficients c_n(k) of f(chi) D(k, chi)).  The
- * coefficients are computed at the plan's n_interp nodes kappa_a = k_0 (k_max / k_0)^{a / (n_interp-1)}
- * (uniform in ln k, both ends included) and continued to every k node by the natural cubic spline in
- * ln k through the node values (its second derivatives within 2e-10 of the exact solve, relative to
- * the moments 17 nodes on, in FP32 arithmetic); the window at k_j uses c_n(k_j), so the inverse transform becomes a
- * dense sum over n per k (run as a GEMM on MFMA).  Growth at a node is continued in z by the natural
- * cubic spline, like D(z).
+ * P(k, z_fid) D(k, z(chi)) D(k, z(chi')), FFTLog coefficients c_n(k) of f(chi) D(k, chi)).  The growth is
+ * given at the plan's n_interp nodes kappa_a = k_0 (k_max / k_0)^{a / (n_interp-1)} (uniform in ln k, both
+ * ends included) and continued to every k node by the natural cubic spline in ln k through the node values,
+ * which is the same as continuing c_n(kappa_a); the sum over n then becomes one over the chi nodes of the
+ * support, a product on MFMA.  Growth at a node is continued in z by the natural cubic spline, like D(z).
  *   D_kz  device, double, [B][n_interp][n_zg]: D(kappa_a, z_geom) of every point; it replaces
  *         in->D_z, which is not read.
  *   C     as for swiftcl_cl (float).
@@ -294,8 +292,9 @@ swiftcl_status swiftcl_cl_kgrowth(swiftcl_plan_t plan, const swiftcl_inputs* in,
                                   void* stream);
 
 /* swiftcl_cl_kgrowth by the sums of its adjoint: the windows from the FFTLog coefficients of every
- * node, continued along ln k, as swiftcl_cl_kgrowth_backward recomputes them (5.1 times slower: 5.7
- * against 1.1 ms for 64 points of 15 tracers and 103 multipoles).  The two entry points agree to FP32
+ * node, continued along ln k (the moments within 2e-10 of the exact solve, relative to those 17 nodes on,
+ * in FP32 arithmetic), as swiftcl_cl_kgrowth_backward recomputes them.  5.5 times slower: 6.2 against
+ * 1.1 ms for 64 points of 15 tracers, 103 multipoles and 200 nodes.  The two entry points agree to FP32
  * rounding.  Same arguments and refusals. */
 swiftcl_status swiftcl_cl_kgrowth_nodes(swiftcl_plan_t plan, const swiftcl_inputs* in, const double* D_kz, void* C,
                                         void* stream);

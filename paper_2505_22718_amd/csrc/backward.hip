@@ -695,9 +695,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
 // per (point, multipole chunk): the windows of a multipole's tracers in registers (wavefront w: tracers w and,
 // NT = 2, w + 16), through LDS a slab of k at a time, Y of every slab into the workspace.  The products take the
 // tracers in the order of k_bwd_gv4 (IT_FIRST: dP row tile by row tile, as k_bwd_gv4 does; else as k_bwd_gv,
-// which grids of n_k not a multiple of 4 had), so the gradients are the same bit for bit.  Bound by the FP32
-// issue of the transforms and, between barriers, of the products: 64 points of 30 tracers, 200 multipoles and
-// n_k = 2048 take 2.24 ms; W through the workspace took 1.13 + 1.82 ms (6.6 GB more).
+// which grids of n_k not a multiple of 4 had), so the gradients are the same bit for bit.  64 points of 30
+// tracers, 200 multipoles and n_k = 2048 take 2.19 ms; W through the workspace took 1.13 + 1.82 ms (6.6 GB more).
+// No unit binds it: vector issue 41% of the cycles, matrix cores 16%, 1.9 TB/s of HBM (3.2 GB of Y written),
+// 16 B of scratch per lane.  A multipole's transforms and its products follow each other between barriers in the
+// one workgroup that a CU holds (k_windows_p runs the same transforms, with a projection, in 1.20 ms), and the
+// products read G and every row of W twice from LDS (32 reads per 16 MFMAs).
 template <int M, int NT> using wy_shape = slab_shape<M, NT, 16, 0>;  // (two rows of a product's read 16 banks apart)
 
 template <int M, int NT, int EXTRA>
@@ -864,9 +867,9 @@ static hipError_t launch_bwd_wy(const plan_dev& p, const swiftcl_inputs* in, con
 // tracer 4 g + w through the chunk's multipoles, dx = 2 s F k^{-1-b} Y from its workspace row,
 // r2c, dc += h conj(X) conj(U_l) in registers, flushed to the (point, chunk, tracer, band)
 // partial row when the band changes; rows of bands the chunk never reaches are left alone (bwd_bands).
-// Bound by the FP32 issue of the transforms; the row of the next multipole is loaded during this one's
-// transform (1.82 -> 1.30 ms for 64 points of 30 tracers, n_chi = 2048; three wavefronts per SIMD, 51 KB
-// of LDS).
+// Bound by the FP32 issue of the transforms (54% of the cycles) and the reads of Y (2.8 TB/s) at three
+// wavefronts per SIMD (51 KB of LDS); the row of the next multipole is loaded during this one's transform
+// (1.82 -> 1.30 ms for 64 points of 30 tracers, n_chi = 2048).
 template <int M>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_bwd_adj(plan_dev P, swiftcl_inputs in, int b0, int nbp, int nlc) {
   constexpr int RL = M / SWIFTCL_WAVE;
@@ -961,9 +964,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
 // LDS rows and the pipeline of k_bwd_windows but the sums of k_bwd_gv4 (the same order of the tracers in
 // every product, dP over a chunk's multipoles per lane) and k_bwd_adj, chunk by chunk: the gradients are
 // the same bit for bit.  One workgroup per CU (120 KB of LDS).  32 points of 15
-// tracers and 103 multipoles with both terms: 288 us (288 chunks in two rounds, 12.5 us per multipole: the FP32
-// issue of two transforms per tracer), against 356 us for the three kernels through the workspace; two tracers
-// on each of 8 wavefronts, two workgroups per CU, took 404 us (spills, two wavefronts per SIMD).
+// tracers and 103 multipoles with both terms: 275 us (288 chunks on 256 CUs, so a second round of 32 workgroups;
+// 12 us per multipole: vector issue 32% of all cycles, twice that while every CU works), against 356 us for the
+// three kernels through the workspace; two tracers on each of 8 wavefronts, two workgroups per CU, took 404 us
+// (spills, two wavefronts per SIMD).
 template <int M> __host__ __device__ constexpr int bwd_rows_vs(int n_k) {
   const int w = n_k > 2 * fft_lds_size(M, 4) ? n_k : 2 * fft_lds_size(M, 4);
   return (w + 63) / 64 * 64 + 16;  // rows q and q + 1 (a half-wave of the products' reads) 16 banks apart

@@ -515,8 +515,8 @@ bool windows_tw_lds(int precision, int M) { return precision != SWIFTCL_FP64 && 
 // per lane.  The rows meet in LDS a slab of k at a time, double-buffered in the space of the transforms'
 // scratch (one barrier per slab), and the Gram tiles (0,0), (0,1), (1,1) accumulate over the slabs on MFMA,
 // so that no window reaches HBM.  Through a workspace (rows written, then read by a contraction) 64 points
-// of 30 tracers, 200 multipoles and n_k = 2048 moved 6.6 GB and took 2.5 ms; this takes 1.30 ms, bound by
-// the FP32 issue of the transforms.
+// of 30 tracers, 200 multipoles and n_k = 2048 moved 6.6 GB and took 2.5 ms; this takes 1.20 ms and 0.24 GB,
+// bound by the FP32 issue of the transforms (68% of the cycles; matrix cores 4%).
 // EXTRA bit 1: the plan carries RSD, bit 2: magnification (used when the inputs give C_g).
 // ---------------------------------------------------------------------------------------------
 template <int M, int NT> using wp_shape = slab_shape<M, NT, 4, NT == 2 ? 3 : 1>;  // 16-byte reads on distinct banks

@@ -11,7 +11,8 @@
 // (k_0 e^{s Delta})^{-(b_beta - b_0)}, is a function of s = j + m alone, so it is folded into K_l and
 // the multipoles of all bands share the rows of one product: per (point, kind)
 //   [multipoles x s] . [s x (tracer, k node)],  right operand g_t(s - j) D_j(s - j),
-// on the 16x16x4 f32 MFMA, writing sqrt(s) W to the workspace for the projection kernel.
+// as three bf16 parts per operand on the 16x16x32 bf16 MFMA, writing sqrt(s) W to the workspace for the
+// projection kernel.
 //
 // (kgrowth.hip has the same windows through the node coefficients, which the gradients use.)
 //
@@ -278,8 +279,9 @@ __device__ __forceinline__ unsigned short bf16_rne_kc(float x) {
 // Both operands are FP32 values as three bf16 each, and six of the nine part products are summed in FP32
 // on the 16x16x32 bf16 MFMA, small ones first (the three left out are below 2^-26 of the product): 2.7 times the rate of the f32
 // MFMA.  64 points of 15 tracers, 103 multipoles, 1024 k nodes and 442 chi nodes: 0.66 ms (1.01 ms on the f32
-// MFMA), 40% of the cycles on the matrix cores and as many on the vector unit (splits, loads); the same
-// windows from the node coefficients (an n-sum of 1024 terms, its 200-node FFTs and splines) take 5.7 ms.
+// MFMA), the matrix cores busy in 39% of the cycles, the vector unit in 34% (splits, loads), 1.2 TB/s of HBM
+// and no bank conflicts: the two units take turns, three wavefronts per SIMD.  The same windows from the node
+// coefficients (an n-sum of 1024 terms, its 200-node FFTs and splines) take 5.7 ms.
 constexpr int KC_RT = 7;            // 16-row multipole tiles per workgroup
 constexpr int KC_SC = 32;           // offsets s per step
 typedef unsigned short v8us __attribute__((ext_vector_type(8)));

@@ -50,8 +50,9 @@ __global__ __launch_bounds__(512) void k_limber_pk(plan_dev P, swiftcl_inputs in
 // sum_m H_i(m) [s_l(m) H_j(m)] on the 16x16x4 MFMA, four nodes per lane and load (both operands take
 // the nodes in the same order).  The factor c(l) / nu^2 (F(l) or l(l+1)) per lensing-kind tracer of
 // the pair is applied at the end.  Bound by the FP64 exp and spline of the weights and the MFMA
-// issue: 189 us for 256 points x 15 tracers x 103 multipoles (445 nodes); with one thread per tracer
-// pair on VALU (120 of 256 threads at work) the kernel took 290 us.
+// issue (vector issue 44% of the cycles, matrix cores 22%): 177 us for 256 points x 15 tracers x 103
+// multipoles (445 nodes); with one thread per tracer pair on VALU (120 of 256 threads at work) the
+// kernel took 290 us.
 constexpr int LB_LG = 8;     // multipole slots per block
 constexpr int LB_CH = 256;   // chi nodes per LDS chunk
 constexpr int LB_HS = LB_CH + 4;  // row stride of H: the 16 rows x 4 node groups of a load on distinct banks
@@ -236,9 +237,10 @@ __global__ void k_limber_zero(plan_dev P, swiftcl_inputs in) {
 // once, lane (c, q) for the group's multipole q and node c.  The ln P cotangents go to LDS (FP64
 // atomics; the nodes of one multipole fall on distinct intervals) and once per block to the point's
 // global rows.  The two halves' dH meet in LDS; the block writes the dg rows of its nodes (band 0; the
-// other bands 0; nodes outside the support are never read).  595 us for 256 points x 15
-// tracers x 103 multipoles (445 nodes), bound by latency at four wavefronts per SIMD; with Q formed by
-// two threads per node from LDS and two barriers per multipole it took 3530 us.
+// other bands 0; nodes outside the support are never read).  567 us for 256 points x 15
+// tracers x 103 multipoles (445 nodes), bound by latency at four wavefronts per SIMD (vector issue 33% of the
+// cycles, matrix cores 14%, LDS 5% without bank conflicts, 0.3 TB/s; 12 B of scratch per lane); with Q formed
+// by two threads per node from LDS and two barriers per multipole it took 3530 us.
 constexpr int LB_BN = 64;  // chi nodes per block of the adjoint
 
 template <typename R, int NT>  // NT: 16-row tracer tiles

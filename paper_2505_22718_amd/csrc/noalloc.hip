@@ -84,8 +84,8 @@ extern "C" swiftcl_status swiftcl_cl_noalloc(swiftcl_plan_t p, const swiftcl_inp
   if (!in) { set_error("inputs is NULL"); return SWIFTCL_E_INVALID; }
   if (!C) { set_error("C is NULL"); return SWIFTCL_E_INVALID; }
   if (!p->d.fused) {
-    set_error("swiftcl_cl_noalloc runs the fused projection only (<= 16 tracers, no rsd or magnification); "
-              "this plan projects through its workspace");
+    set_error("swiftcl_cl_noalloc runs the fused projection only (<= 16 tracers whose windows fit LDS, no rsd or "
+              "magnification); this plan runs the other one");
     return SWIFTCL_E_UNSUPPORTED;
   }
   if (in->batch >= 1 && in->batch <= p->d.max_batch) {

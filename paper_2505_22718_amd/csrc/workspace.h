@@ -1,8 +1,9 @@
 // Points that the chunked workspace of a plan holds.  Plain C++ (no HIP) so that a host test can check it.
 //
-// The paths that run through the workspace take the points in chunks and give the same bits for every chunk
-// size: larger chunks only fill the chip better.  So a plan needs `base` points of V rows (what its multipole
-// chunks are sized for) and takes more as long as half of the device's free memory is left to others.
+// The paths that run through the workspace take the points in chunks, and a point's results do not depend on
+// its chunk (the gradients not by a bit, C of growth not beyond rounding): larger chunks only fill the chip
+// better.  So a plan needs `base` points of V rows (what its multipole chunks are sized for) and takes more as
+// long as half of the device's free memory is left to others.
 #pragma once
 
 #include <stddef.h>

@@ -86,8 +86,11 @@ class ClKgrowthFunction(torch.autograd.Function):
         ctx.plan = plan
         ctx.t = t
         ctx.D = D
-        # torch checks at backward time that none of these was modified in place since
-        ctx.save_for_backward(D_kz, pk, bias)
+        # the windows of the backward pass are recomputed from all of these: torch checks at backward time that
+        # none was modified in place since (it does not track a tensor made in inference mode, nor save it)
+        kept = [D_kz, pk, bias] + [x for n, x in inputs.items()  # (D_kz takes the place of D_z)
+                                   if n not in ("pk", "bias", "D_z") and isinstance(x, torch.Tensor)]
+        ctx.save_for_backward(*[x for x in kept if not x.is_inference()])
         return C
 
     @staticmethod

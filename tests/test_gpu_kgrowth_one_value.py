@@ -53,11 +53,35 @@ def test_one_value(dev, grads, precision):
             assert leaves[n].grad is None
 
 
-def test_inputs_changed_before_backward_are_refused(dev):
+@pytest.mark.parametrize("name", ["D_kz", "nz", "bias"])
+def test_inputs_changed_before_backward_are_refused(dev, name):
+    from paper_2505_22718_amd import autograd
+    p, t, D = _setup(dev)
+    pk = t["pk"].clone().requires_grad_(True)
+    C = autograd.cl_kgrowth(p, t, D, pk, t["bias"])
+    (D if name == "D_kz" else t[name]).mul_(1.1)
+    with pytest.raises(RuntimeError, match="modified by an inplace operation"):
+        C.sum().backward()
+
+
+def test_the_growth_that_D_kz_replaces_may_change(dev):
     from paper_2505_22718_amd import autograd
     p, t, D = _setup(dev)
     bias = t["bias"].clone().requires_grad_(True)
     C = autograd.cl_kgrowth(p, t, D, t["pk"], bias)
-    D.mul_(1.1)
-    with pytest.raises(RuntimeError, match="modified by an inplace operation"):
-        C.sum().backward()
+    t["D_z"].mul_(2.0)
+    C.sum().backward()
+    assert bool(torch.isfinite(bias.grad).all())
+
+
+def test_growth_from_inference_mode(dev):
+    from paper_2505_22718_amd import autograd
+    p, t, D = _setup(dev)
+    with torch.inference_mode():
+        Di = D * 1.0
+    g = []
+    for growth in (D, Di):
+        pk = t["pk"].clone().requires_grad_(True)
+        autograd.cl_kgrowth(p, t, growth, pk, t["bias"]).sum().backward()
+        g.append(pk.grad)
+    assert bool(torch.equal(*g))
